@@ -24,7 +24,7 @@ METRIC = "BAPS attention fwd TFLOP/s + % bf16 MFMA peak (prefill); decode HBM GB
 PEAK_BF16_TFLOPS = 2500.0        # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 CSRC = os.path.join(ROOT, "paper_2602_02071_amd", "csrc")
-KERNEL_SRC = {"attn_fwd_prefill": "attn_fwd.hip", "attn_fwd_decode": "attn_decode.hip"}
+KERNEL_SRC = {"attn_fwd_prefill": "attn_fwd.hpp", "attn_fwd_decode": "attn_decode.hip"}
 
 
 def _src_hash(path):

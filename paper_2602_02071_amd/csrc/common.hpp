@@ -25,6 +25,21 @@ struct DeviceOnce {
     }
 };
 
+// Compute units of the current device, read once per device ordinal below 64.
+inline hipError_t cu_count(int* ncu)
+{
+    static std::atomic<int> count[64] = {};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const bool kept = dev >= 0 && dev < 64;
+    *ncu = kept ? count[dev].load(std::memory_order_relaxed) : 0;
+    if (*ncu) return hipSuccess;
+    e = hipDeviceGetAttribute(ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess && kept) count[dev].store(*ncu, std::memory_order_relaxed);
+    return e;
+}
+
 typedef __bf16 bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef float f32x16 __attribute__((__vector_size__(16 * sizeof(float))));
 typedef float f32x4 __attribute__((__vector_size__(4 * sizeof(float))));
@@ -205,6 +220,7 @@ hipError_t launch_hif8_encode(const float* x, uint8_t* codes, long long n, bool 
 hipError_t launch_hif8_decode(const uint8_t* codes, float* x, long long n, hipStream_t st);
 hipError_t launch_softmax_block(const SoftmaxBlockParams& p, hipStream_t st);
 hipError_t launch_attention(const AttnParams& p, int D, int block, hipStream_t st);
+hipError_t launch_attention_dump(const AttnParams& p, int D, int block, hipStream_t st);
 hipError_t launch_attention_decode(const AttnParams& p, int D, int block, hipStream_t st);
 hipError_t launch_attention_split(const SplitParams& sp, int D, int block, hipStream_t st);
 
