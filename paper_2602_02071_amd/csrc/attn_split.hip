@@ -12,7 +12,7 @@
 //   2. pv: every split in parallel first replays Alg. 1's B0 / restart rule
 //      and integer maximum over the block maxima of its rows, from block 0 to
 //      its own last block -- the same per-block decision as the one-pass
-//      kernels, 16 blocks per step, serial only where m changes -- then
+//      kernels, many blocks per step, serial only where m changes -- then
 //      streams V, forms P = HiF8(2^HiF8(T)) with T = fl32(acc*c - ref_j), and
 //      accumulates X and dX relative to its latest reference;
 //   3. combine: per row, the splits' X and dX brought to the largest
@@ -20,6 +20,8 @@
 //      row) and summed: O = sum X / sum dX, and lse.
 // Every T, P and reference equals the one-pass kernels'; O differs only by
 // the order of the fp32 additions.
+
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_scores_kernel(SplitPara
 // ---------------------------------------------------------------------------
 // 2. pv: Alg. 1's per-block decisions up to the split, then P V of the split
 // ---------------------------------------------------------------------------
-constexpr int kWinBlocks = 256;      // block maxima per LDS window of the scan (one row)
+constexpr int kWinFloats = 256;      // block maxima per LDS window of the replay
 
 template <int D, int BLK>
 struct PCfg {
@@ -279,7 +281,8 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     constexpr int PS = PC::kPS;
     __shared__ __attribute__((aligned(1024))) uint8_t ctab[kCodeTableBytes];   // entry i at [i - kCodeLo]
     __shared__ unsigned s_cnt[kRows][2];
-    __shared__ __attribute__((aligned(1024))) float s_win[KW][2][kWinBlocks];       // scan windows
+    constexpr int kWinBufs = 8 / KW;              // windows in flight per wave (8 KiB in all)
+    __shared__ __attribute__((aligned(1024))) float s_win[KW][kWinBufs][kWinFloats];
     __shared__ float refs_l[kRows * kSplitMaxBps];                                   // block references
     extern __shared__ __attribute__((aligned(1024))) char ring[];
     const uint32_t ring_lds = (uint32_t)(uintptr_t)LDS_PTR(char, ring);
@@ -303,32 +306,34 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     const float ninf = -__builtin_huge_valf();
     const float c = p.c;
 
-    // -- block-maximum windows of the scan: one wave-wide 1 KiB DMA each, the
-    //    maxima of blocks [256 w, 256 w + 256) of one row of the tile
-    const uint32_t win_lds = (uint32_t)(uintptr_t)LDS_PTR(float, &s_win[wave][0][0]);
-    const float* win = &s_win[wave][0][0];
-    const int nwin = (j1 + kWinBlocks - 1) / kWinBlocks;
+    // -- block-maximum windows of the replay: a wave replays RPW rows at a
+    //    time, L = 64/RPW lanes per row, and one wave-wide 1 KiB DMA brings the
+    //    maxima of 4 L blocks of each of them
     const int nr = min(kRows, flat - tile * kRows);         // rows of the tile (at least one)
-    const int npass = (nr + KW - 1) / KW;                   // the scan takes one row per wave at a time
+    const int rpw = nr <= KW ? 1 : (nr <= 2 * KW ? 2 : 4);
+    const int npass = (nr + KW * rpw - 1) / (KW * rpw);
+    const int wblk = kWinFloats / rpw;                       // blocks per window and row
+    const int nwin = (j1 + wblk - 1) / wblk;
+    const int nall = npass * nwin;                           // windows of this wave, pass by pass
+    const uint32_t win_lds = (uint32_t)(uintptr_t)LDS_PTR(float, &s_win[wave][0][0]);
     int ndma = 0;                                 // DMA ops of this wave issued so far
-    int tag0 = 0, tag1 = 0;                       // ndma after the DMA of each window buffer
-    int tagc = 0;                                 // ndma after this wave's part of the code table
     {
         const uint32_t ctab_lds = (uint32_t)(uintptr_t)LDS_PTR(uint8_t, ctab);
         for (int i = wave; i < kCodeTableBytes / 1024; i += KW) {
             lds_dma_16(p.ctab + i * 1024 + 16 * lane, ctab_lds + (uint32_t)(i * 1024));
-            tagc = ++ndma;
+            ++ndma;
         }
     }
-    auto issue_win = [&](int pass, int w) {
-        const int srow = min(pass * KW + wave, nr - 1);
-        const float* src = sp.bmax + (bg * flat + tile * kRows + srow) * sp.bstride + w * kWinBlocks + 4 * lane;
-        lds_dma_16(src, win_lds + (uint32_t)((w & 1) * 1024));
+    const int tagc = ndma;                        // ndma after this wave's part of the code table
+    auto issue_win = [&](int i) {
+        const int lpr = 64 / rpw;
+        const int srow = min((i / nwin * KW + wave) * rpw + lane / lpr, nr - 1);
+        const float* src = sp.bmax + (bg * flat + tile * kRows + srow) * sp.bstride + (i % nwin) * wblk + 4 * (lane % lpr);
+        lds_dma_16(src, win_lds + (uint32_t)((i % kWinBufs) * 1024));
         ++ndma;
-        if (w & 1) tag1 = ndma; else tag0 = ndma;
     };
-    issue_win(0, 0);
-    if (nwin > 1) issue_win(0, 1);
+    const int nearly = min(nall, kWinBufs);       // windows issued ahead of the V ring
+    for (int i = 0; i < nearly; ++i) issue_win(i);
 
     // -- the V ring of this split
     const uint32_t my_ring_lds = ring_lds + (uint32_t)(wave * RW * C::kSlotBytes);
@@ -348,73 +353,89 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     int issued = 0;
     for (; issued < min(nslots, RW); ++issued) issue_slot(issued);
 
-    // -- the scan: Alg. 1's decision for every block of [0, j1) of a row, 64
+    // -- the replay: Alg. 1's decision for every block of [0, j1) of a row, L
     //    blocks (one per lane) evaluated per step at the current m; the blocks
     //    up to the first one that changes m are settled, and the step repeats
-    //    from there with the new m (wave-uniform: a scalar register)
-    const float lam = (float)p.lambda;
-    for (int pass = 0; pass < npass; ++pass) {
-        const int srow = pass * KW + wave;
-        const bool row_ok = srow < nr;
-        const int last_blk = row_ok ? row_info(p, tile, g, srow).kmax / BLK : -1;   // B0 with b0_last
-        float m = ninf;
-        unsigned n_restart = 0, n_visit = 0;
-        if (pass > 0) {                           // this pass's first windows (the V ring is already in flight)
-            issue_win(pass, 0);
-            if (nwin > 1) issue_win(pass, 1);
-        }
-        for (int w = 0; w < nwin; ++w) {
-            wait_vm(ndma - ((w & 1) ? tag1 : tag0));
-            const float* wl = win + (w & 1) * kWinBlocks;
+    //    from there with the new m.  It is a serial chain of short steps in
+    //    front of P V, so the rows of a tile share a wave's lanes instead of
+    //    taking turns: with one row per wave at a time, 6 queries of 4 heads on
+    //    3000 keys spent 23 of the kernel's 33 us here.
+    const int tagv = ndma;                        // ndma after the V ring's first loads
+    auto wait_win = [&](int i) { wait_vm(ndma - (i < nearly ? tagc + i + 1 : tagv + (i - nearly) + 1)); };
+    const float* win = &s_win[wave][0][0];
+    auto replay = [&](auto rows_per_wave) {
+        constexpr int RPW = decltype(rows_per_wave)::value;
+        constexpr int L = 64 / RPW, kWB = kWinFloats / RPW;
+        const int sl = lane % L, sg = lane / L;   // this lane's block of the step, and its row
+        for (int pass = 0; pass < npass; ++pass) {
+            const int srow = (pass * KW + wave) * RPW + sg;
+            const bool row_ok = srow < nr;
+            const int last_blk = row_ok ? row_info(p, tile, g, srow).kmax / BLK : -1;   // B0 with b0_last
+            float m = ninf;
+            unsigned n_restart = 0, n_visit = 0;
+            for (int w = 0; w < nwin; ++w) {
+                const int i = pass * nwin + w;
+                wait_win(i);
+                const float* wl = win + (i % kWinBufs) * kWinFloats + sg * kWB;
 #pragma unroll 1
-            for (int kk = 0; kk < kWinBlocks / 64; ++kk) {
-                const int cb = w * kWinBlocks + 64 * kk;
-                if (cb >= j1) break;
-                const int jb = cb + lane;
-                float amax = wl[64 * kk + lane];
-                if (!(row_ok && jb < j1)) amax = ninf;
-                const bool vis = amax != ninf;
-                const float ceil_ac = ceilf(amax * c);
-                const bool in_b0 = jb < p.n_b0 || (p.b0_last && jb == last_blk);
-                const bool mine = row_ok && jb >= j0 && jb < j1;
-                int lo = 0;
-                for (;;) {
-                    const bool forced = in_b0 || (m == ninf);
-                    const float tq = hif8::round(__builtin_fmaf(amax, c, -m));
-                    const bool restart = forced || (ceilf(tq) > lam);
-                    const float m_hi = __builtin_fmaxf(m, ceil_ac);
-                    const float m_new = vis ? (restart ? m_hi : m + __builtin_fmaxf(0.0f, ceilf(tq))) : m;
-                    const float ref_new = vis ? (restart ? m_hi : m) : ninf;
-                    const bool pend = lane >= lo;
-                    const unsigned long long bal = __ballot(pend && hif8::f2u(m_new) != hif8::f2u(m));
-                    const int f = bal ? (int)__builtin_ctzll(bal) : 64;
-                    if (pend && lane <= f && mine) {
-                        refs_l[srow * kSplitMaxBps + (jb - j0)] = ref_new;   // -inf: no visible key
-                        const bool b1 = vis && !in_b0;
-                        n_visit += b1 ? 1u : 0u;
-                        n_restart += (b1 && restart) ? 1u : 0u;
+                for (int kk = 0; kk < kWB / L; ++kk) {
+                    const int cb = w * kWB + L * kk;
+                    if (cb >= j1) break;
+                    const int jb = cb + sl;
+                    float amax = wl[L * kk + sl];
+                    if (!(row_ok && jb < j1)) amax = ninf;
+                    const bool vis = amax != ninf;
+                    const float ceil_ac = ceilf(amax * c);
+                    const bool in_b0 = jb < p.n_b0 || (p.b0_last && jb == last_blk);
+                    const bool mine = row_ok && jb >= j0 && jb < j1;
+                    int lo = 0;
+                    for (;;) {
+                        // (the restart test and the increment as in the
+                        // prefill kernel: lambda <= kCodeMaxLambda here)
+                        const bool forced = in_b0 || (m == ninf);
+                        const float xt = __builtin_fmaf(amax, c, -m);
+                        const bool restart = forced || (xt >= p.dec_x0);
+                        const float m_hi = __builtin_fmaxf(m, ceil_ac);
+                        const float m_new = vis ? (restart ? m_hi : m + hif8_ceil_below9(xt)) : m;
+                        const float ref_new = vis ? (restart ? m_hi : m) : ninf;
+                        const bool pend = sl >= lo;
+                        const unsigned long long bal = __ballot(pend && hif8::f2u(m_new) != hif8::f2u(m));
+                        const unsigned long long mine_bal = RPW == 1 ? bal : (bal >> (sg * L)) & ((1ull << (L & 63)) - 1);
+                        const int f = mine_bal ? (int)__builtin_ctzll(mine_bal) : L;   // this row's first change of m
+                        if (pend && sl <= f && mine) {
+                            refs_l[srow * kSplitMaxBps + (jb - j0)] = ref_new;   // -inf: no visible key
+                            const bool b1 = vis && !in_b0;
+                            n_visit += b1 ? 1u : 0u;
+                            n_restart += (b1 && restart) ? 1u : 0u;
+                        }
+                        if constexpr (RPW == 1) {             // (wave-uniform: a scalar register)
+                            if (f < 64) m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(
+                                                __builtin_bit_cast(int, m_new), f & 63));
+                            if (f >= 63) break;
+                        } else {
+                            const float at = __shfl(m_new, sg * L + min(f, L - 1), 64);
+                            m = f < L ? at : m;
+                            if (!__any(f < L - 1)) break;
+                        }
+                        lo = f + 1;
                     }
-                    if (f >= 63) {
-                        if (f == 63) m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(
-                                              __builtin_bit_cast(int, m_new), 63));
-                        break;
-                    }
-                    m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, m_new), f));
-                    lo = f + 1;
                 }
+                if (i + kWinBufs < nall) issue_win(i + kWinBufs);
             }
-            if (w + 2 < nwin) issue_win(pass, w + 2);
-        }
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            n_visit += __shfl_xor(n_visit, o, 64);
-            n_restart += __shfl_xor(n_restart, o, 64);
+            for (int o = 1; o < L; o <<= 1) {
+                n_visit += __shfl_xor(n_visit, o, 64);
+                n_restart += __shfl_xor(n_restart, o, 64);
+            }
+            if (sl == 0 && row_ok) {
+                s_cnt[srow][0] = n_restart;
+                s_cnt[srow][1] = n_visit;
+            }
         }
-        if (lane == 0 && row_ok) {
-            s_cnt[srow][0] = n_restart;
-            s_cnt[srow][1] = n_visit;
-        }
-    }
+    };
+    if (rpw == 1) replay(std::integral_constant<int, 1>{});
+    else if (rpw == 2) replay(std::integral_constant<int, 2>{});
+    else replay(std::integral_constant<int, 4>{});
     wait_vm(ndma - tagc);                         // this wave's part of the code table has landed
 
     const RowInfo ri = row_info(p, tile, g, c16);
@@ -667,7 +688,7 @@ hipError_t launch_split_db(const SplitParams& sp, hipStream_t st)
         attr_set.mark(dev);
     }
     const AttnParams& p = sp.a;
-    if (sp.bps < 1 || sp.bps > kSplitMaxBps || sp.bstride % kWinBlocks || sp.bstride < sp.nblk ||
+    if (sp.bps < 1 || sp.bps > kSplitMaxBps || sp.bstride % kWinFloats || sp.bstride < sp.nblk ||
         (long long)sp.nsplit * sp.bps < sp.nblk || (long long)(sp.nsplit - 1) * sp.bps >= sp.nblk)
         return hipErrorInvalidValue;
     const long long flat = (long long)p.Sq * (p.Hq / p.Hkv);
