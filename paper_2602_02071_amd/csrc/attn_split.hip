@@ -38,16 +38,24 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast
 constexpr int kRows = 16;            // query rows per workgroup (16x16x32 MFMA columns)
 constexpr int kSlotKeys = 32;        // keys per wave and block, and per ring slot
 
-template <int D, int BLK>
+// A workgroup's waves are KW key slots (wave % KW takes 32 keys of a block)
+// times BG block groups (wave / KW takes every BG-th block of the split: the
+// blocks are independent once the references are known).  Two workgroups of
+// four waves share a CU, or, where the grid holds at most one per CU (BIG),
+// one of eight with twice the LDS: either way eight waves hide each other's
+// latency and 128 KiB of ring keep the memory busy.
+template <int D, int BLK, bool BIG>
 struct SCfg {
-    static constexpr int kWaves = BLK / kSlotKeys;              // one wave per 32-key slot of a block
+    static constexpr int kWaves = BIG ? 8 : 4;
+    static constexpr int kKeySlots = BLK / kSlotKeys;
+    static constexpr int kGroups = kWaves / kKeySlots;
     static constexpr int kRowBytes = 2 * D;
     static constexpr int kCPR = D / 8;                          // 16-byte chunks per row
     static constexpr int kSlotBytes = kSlotKeys * kRowBytes;
     static constexpr int kIPS = kSlotBytes / 1024;              // wave-wide loads per slot
-    static constexpr int kRW0 = (64 * 1024) / (kWaves * kSlotBytes);
-    static constexpr int kRW = kRW0 < 2 ? 2 : (kRW0 * kIPS > 63 ? 63 / kIPS : kRW0);
+    static constexpr int kRW = ((BIG ? 128 : 64) * 1024) / (kWaves * kSlotBytes);   // ring slots per wave
     static constexpr int kLdsBytes = kWaves * kRW * kSlotBytes;
+    static_assert(kRW >= 2 && kRW * kIPS <= 63, "ring slots");
 };
 
 template <int D>
@@ -108,14 +116,17 @@ __device__ __forceinline__ RowInfo row_info(const AttnParams& p, int tile, int g
 // ---------------------------------------------------------------------------
 // 1. scores: acc and block maxima of one key split
 // ---------------------------------------------------------------------------
-template <int D, int BLK, bool F8>
-__global__ __launch_bounds__(64 * (BLK / 32)) void split_scores_kernel(SplitParams sp)
+template <int D, int BLK, bool F8, int RT, bool BIG>
+__global__ __launch_bounds__(BIG ? 512 : 256, 2) void split_scores_kernel(SplitParams sp)
 {
-    using C = SCfg<D, BLK>;
-    constexpr int KW = C::kWaves;
+    using C = SCfg<D, BLK, BIG>;
+    constexpr int NW = C::kWaves, KW = C::kKeySlots, BG = C::kGroups;
     constexpr int RW = C::kRW;
     constexpr int kDK = D / 32;
-    __shared__ float xch[2][KW][kRows];
+    constexpr int kTR = RT * kRows;              // rows of the workgroup
+    // row maxima of this wave's keys of every block of the split; the waves
+    // meet once, after the last block
+    __shared__ float wmax[kSplitMaxBps / RT][KW][kTR];
     extern __shared__ __attribute__((aligned(1024))) char ring[];
     const uint32_t ring_lds = (uint32_t)(uintptr_t)LDS_PTR(char, ring);
     const AttnParams& p = sp.a;
@@ -123,6 +134,7 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_scores_kernel(SplitPara
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kw = wave % KW, bg0 = wave / KW;    // key slot and block group of this wave
     const int c16 = lane & 15;
     const int grp = lane >> 4;
     const int split = blockIdx.x % sp.nsplit;
@@ -135,13 +147,14 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_scores_kernel(SplitPara
     const uint8_t* kbase8 = reinterpret_cast<const uint8_t*>(p.k) + bg * (long long)p.Sk * D;
     const int j0 = split * sp.bps;
     const int j1 = min(sp.nblk, j0 + sp.bps);
-    const int nslots = max(0, j1 - j0);
+    const int nslots = max(0, j1 - j0);                  // blocks of the split, and of this wave
+    const int mine = max(0, (nslots - bg0 + BG - 1) / BG);
     constexpr int kIPS = F8 ? kSlotKeys * D / 1024 : C::kIPS;     // loads per slot (FP8 K: rows of D bytes)
 
     const uint32_t my_ring_lds = ring_lds + (uint32_t)(wave * RW * C::kSlotBytes);
     const char* my_ring = ring + wave * RW * C::kSlotBytes;
-    auto issue_slot = [&](int n) {               // K keys [32*wave, +32) of block j0 + n
-        const int key0 = (j0 + n) * BLK + wave * kSlotKeys;
+    auto issue_slot = [&](int n) {               // K keys [32*kw, +32) of this wave's n-th block
+        const int key0 = (j0 + bg0 + BG * n) * BLK + kw * kSlotKeys;
         const uint32_t dst = my_ring_lds + (uint32_t)((n % RW) * C::kSlotBytes);
         if constexpr (F8) {
 #pragma unroll
@@ -162,37 +175,48 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_scores_kernel(SplitPara
         }
     };
     int issued = 0;
-    for (; issued < min(nslots, RW); ++issued) issue_slot(issued);
+    for (; issued < min(mine, RW); ++issued) issue_slot(issued);
 
-    const RowInfo ri = row_info(p, tile, g, c16);
-    int kmax_lo = ri.ok ? ri.kmax : 0x7fffffff;
+    RowInfo ri[RT];
+    int kmax_lo = 0x7fffffff;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        ri[rt] = row_info(p, tile * RT + rt, g, c16);
+        if (ri[rt].ok) kmax_lo = min(kmax_lo, ri[rt].kmax);
+    }
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) kmax_lo = min(kmax_lo, __shfl_xor(kmax_lo, o, 64));
     kmax_lo = __builtin_amdgcn_readfirstlane(kmax_lo);
-    u32x4 qop[F8 ? 1 : kDK];
-    i32x8 qop8 = {};                              // FP8: Q[row][32*grp .. +32], zeros past D
-    if constexpr (F8) {
-        const uint8_t* qrow = reinterpret_cast<const uint8_t*>(p.q) + (((long long)b * p.Hq + ri.h) * p.Sq + ri.r) * D;
-        if (ri.ok && 32 * grp < D)
-            qop8 = cat8(*reinterpret_cast<const u32x4*>(qrow + 32 * grp),
-                        *reinterpret_cast<const u32x4*>(qrow + 32 * grp + 16));
-    } else {
-        const uint16_t* qrow = p.q + (((long long)b * p.Hq + ri.h) * p.Sq + ri.r) * D;
+    u32x4 qop[RT][F8 ? 1 : kDK];
+    i32x8 qop8[RT] = {};                          // FP8: Q[row][32*grp .. +32], zeros past D
 #pragma unroll
-        for (int kk = 0; kk < kDK; ++kk)
-            qop[kk] = ri.ok ? *reinterpret_cast<const u32x4*>(qrow + kk * 32 + grp * 8) : u32x4{0, 0, 0, 0};
+    for (int rt = 0; rt < RT; ++rt) {
+        const long long qoff = (((long long)b * p.Hq + ri[rt].h) * p.Sq + ri[rt].r) * D;
+        if constexpr (F8) {
+            const uint8_t* qrow = reinterpret_cast<const uint8_t*>(p.q) + qoff;
+            if (ri[rt].ok && 32 * grp < D)
+                qop8[rt] = cat8(*reinterpret_cast<const u32x4*>(qrow + 32 * grp),
+                                *reinterpret_cast<const u32x4*>(qrow + 32 * grp + 16));
+        } else {
+            const uint16_t* qrow = p.q + qoff;
+#pragma unroll
+            for (int kk = 0; kk < kDK; ++kk)
+                qop[rt][kk] = ri[rt].ok ? *reinterpret_cast<const u32x4*>(qrow + kk * 32 + grp * 8) : u32x4{0, 0, 0, 0};
+        }
     }
     const float ninf = -__builtin_huge_valf();
     const int kx = k_swz<D>(c16);
     const uint32_t krow = c16 * C::kRowBytes;
     const long long nkeys = (long long)sp.nblk * BLK;
-    float* acc_row = sp.acc + (bg * flat + (ri.ok ? ri.f : 0)) * nkeys;
-    float* bmax_row = sp.bmax + (bg * flat + (ri.ok ? ri.f : 0)) * sp.bstride;
+    const long long row0 = bg * flat + (long long)tile * kTR;    // the workgroup's first row
+    float* acc_row[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc_row[rt] = sp.acc + (bg * flat + (ri[rt].ok ? ri[rt].f : 0)) * nkeys;
 
-    for (int n = 0; n < nslots; ++n) {
-        const int jb = j0 + n;
-        const int key0 = jb * BLK + wave * kSlotKeys;
-        f32x4 sacc[2];
+    for (int n = 0; n < mine; ++n) {
+        const int nb = bg0 + BG * n;              // block of the split
+        const int key0 = (j0 + nb) * BLK + kw * kSlotKeys;
+        f32x4 sacc[RT][2];
         wait_vm((issued - 1 - n) * kIPS);
         const char* slot = my_ring + (n % RW) * C::kSlotBytes;
         if constexpr (F8) {
@@ -205,53 +229,64 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_scores_kernel(SplitPara
                     a8 = cat8(*reinterpret_cast<const u32x4*>(kr + 16 * ((2 * grp) ^ kx8)),
                               *reinterpret_cast<const u32x4*>(kr + 16 * ((2 * grp + 1) ^ kx8)));
                 }
-                sacc[t2] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, qop8, f32x4{}, 0, 0, 0, 127, 0, 127);
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    sacc[rt][t2] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a8, qop8[rt], f32x4{}, 0, 0, 0, 127, 0, 127);
             }
         } else {
 #pragma unroll
             for (int t2 = 0; t2 < 2; ++t2) {
-                f32x4 a4 = {};
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) sacc[rt][t2] = f32x4{};
 #pragma unroll
                 for (int kk = 0; kk < kDK; ++kk) {
                     const u32x4 a = *reinterpret_cast<const u32x4*>(
                         slot + krow + t2 * 16 * C::kRowBytes + 16 * ((4 * kk + grp) ^ kx));
-                    a4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(qop[kk]), a4, 0, 0, 0);
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        sacc[rt][t2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(qop[rt][kk]),
+                                                                              sacc[rt][t2], 0, 0, 0);
                 }
-                sacc[t2] = a4;
             }
         }
-        if (issued < nslots) { issue_slot(issued); ++issued; }
+        if (issued < mine) { issue_slot(issued); ++issued; }
         // mask keys past kmax; register i of tile t2 holds key key0 + 16*t2 + 4*grp + i
         if (key0 + kSlotKeys - 1 > kmax_lo) {
             asm volatile("" ::: "memory");
-            const int lim = ri.kmax - key0 - 4 * grp;
 #pragma unroll
-            for (int t2 = 0; t2 < 2; ++t2)
+            for (int rt = 0; rt < RT; ++rt) {
+                const int lim = ri[rt].kmax - key0 - 4 * grp;
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (16 * t2 + i > lim) sacc[t2][i] = ninf;
-        }
-        if (ri.ok) {
+                for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
-            for (int t2 = 0; t2 < 2; ++t2)
-                *reinterpret_cast<f32x4*>(acc_row + key0 + 16 * t2 + 4 * grp) = sacc[t2];
-        }
-        float pm = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf(sacc[0][0], sacc[0][1]), sacc[0][2]),
-                                   __builtin_fmaxf(__builtin_fmaxf(sacc[0][3], sacc[1][0]), sacc[1][1]));
-        pm = __builtin_fmaxf(pm, __builtin_fmaxf(sacc[1][2], sacc[1][3]));
-        pm = __builtin_fmaxf(pm, __shfl_xor(pm, 16, 64));
-        pm = __builtin_fmaxf(pm, __shfl_xor(pm, 32, 64));
-        if constexpr (KW > 1) {
-            if (grp == 0) xch[jb & 1][wave][c16] = pm;
-            __syncthreads();
-            if (wave == 0) {
-                float am = xch[jb & 1][0][c16];
-#pragma unroll
-                for (int w = 1; w < KW; ++w) am = __builtin_fmaxf(am, xch[jb & 1][w][c16]);
-                pm = am;
+                    for (int i = 0; i < 4; ++i)
+                        if (16 * t2 + i > lim) sacc[rt][t2][i] = ninf;
             }
         }
-        if (wave == 0 && grp == 0 && ri.ok) bmax_row[jb] = pm;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            if (ri[rt].ok) {
+#pragma unroll
+                for (int t2 = 0; t2 < 2; ++t2)
+                    *reinterpret_cast<f32x4*>(acc_row[rt] + key0 + 16 * t2 + 4 * grp) = sacc[rt][t2];
+            }
+            const f32x4 *s0 = &sacc[rt][0], *s1 = &sacc[rt][1];
+            float pm = __builtin_fmaxf(__builtin_fmaxf(__builtin_fmaxf((*s0)[0], (*s0)[1]), (*s0)[2]),
+                                       __builtin_fmaxf(__builtin_fmaxf((*s0)[3], (*s1)[0]), (*s1)[1]));
+            pm = __builtin_fmaxf(pm, __builtin_fmaxf((*s1)[2], (*s1)[3]));
+            pm = __builtin_fmaxf(pm, __shfl_xor(pm, 16, 64));
+            pm = __builtin_fmaxf(pm, __shfl_xor(pm, 32, 64));
+            if (grp == 0) wmax[nb][kw][rt * kRows + c16] = pm;
+        }
+    }
+    __syncthreads();
+    const int nr = min(kTR, flat - tile * kTR);
+    for (int i = tid; i < nr * nslots; i += 64 * NW) {
+        const int row = i / nslots, n = i - row * nslots;
+        float m = wmax[n][0][row];
+#pragma unroll
+        for (int w = 1; w < KW; ++w) m = __builtin_fmaxf(m, wmax[n][w][row]);
+        sp.bmax[(row0 + row) * sp.bstride + j0 + n] = m;
     }
 }
 
@@ -260,30 +295,50 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_scores_kernel(SplitPara
 // ---------------------------------------------------------------------------
 constexpr int kWinFloats = 256;      // block maxima per LDS window of the replay
 
-template <int D, int BLK>
-struct PCfg {
-    using C = SCfg<D, BLK>;
-    static constexpr int kWaves = C::kWaves;
-    static constexpr int kThreads = 64 * kWaves;
-    static constexpr int kPS = D + 4;                            // floats per part row: X, dX, reference
-    static constexpr int kLdsBytes = C::kLdsBytes;               // dynamic: the V ring (64 KiB at most)
-};
-
-template <int D, int BLK>
-__global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams sp)
+// Lanes in groups of L (16, 32 or 64): the maximum of v over the lower lanes of
+// the group, -inf for its first lane
+template <int L>
+__device__ __forceinline__ float prefix_max_before(float v)
 {
-    using C = SCfg<D, BLK>;
-    using PC = PCfg<D, BLK>;
-    constexpr int KW = C::kWaves;
+    const float ninf = -__builtin_huge_valf();
+    const int ni = __builtin_bit_cast(int, ninf);
+#define BAPS_STEP(CTRL, ROWS)                                                                                     \
+    v = __builtin_fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(ni, __builtin_bit_cast(int, v),  \
+                                                                                 CTRL, ROWS, 0xF, false)))
+    BAPS_STEP(0x111, 0xF);                        // row_shr 1, 2, 4, 8: inclusive maxima within 16 lanes
+    BAPS_STEP(0x112, 0xF);
+    BAPS_STEP(0x114, 0xF);
+    BAPS_STEP(0x118, 0xF);
+    if constexpr (L >= 32) BAPS_STEP(0x142, 0xA);   // lane 15 of rows 0 and 2 to rows 1 and 3
+    if constexpr (L == 64) BAPS_STEP(0x143, 0xC);   // lane 31 to rows 2 and 3
+#undef BAPS_STEP
+    const float before = __shfl_up(v, 1, 64);
+    return (threadIdx.x & (L - 1)) == 0 ? ninf : before;
+}
+
+// RT tiles of 16 rows per workgroup share every V (and, in the scores pass, K) read.
+template <int D, int BLK, int RT, bool BIG>
+__global__ __launch_bounds__(BIG ? 512 : 256, 2) void split_pv_kernel(SplitParams sp)
+{
+    using C = SCfg<D, BLK, BIG>;
+    constexpr int NW = C::kWaves, KW = C::kKeySlots, BG = C::kGroups;
     constexpr int RW = C::kRW;
     constexpr int kDT = D / 16;
-    constexpr int NT = PC::kThreads;
-    constexpr int PS = PC::kPS;
+    constexpr int NT = 64 * NW;
+    constexpr int PS = D + 4;                     // floats per partial: X, dX, reference, two spare
+    constexpr int kTR = RT * kRows;              // rows of the workgroup
+    constexpr int kMaxBps = kSplitMaxBps / RT;
+    // The ring carries the split's raw dot products beside V: one slot holds
+    // those of kRun blocks (32 keys x kTR rows x 4 B per block and wave), in
+    // front of the V slots of the same blocks.
+    constexpr int kAccBytes = kSlotKeys * kTR * 4;
+    constexpr int kRun = C::kSlotBytes / kAccBytes;
+    static_assert(kRun >= 1 && kRun * kAccBytes == C::kSlotBytes, "a slot holds whole blocks of dot products");
     __shared__ __attribute__((aligned(1024))) uint8_t ctab[kCodeTableBytes];   // entry i at [i - kCodeLo]
-    __shared__ unsigned s_cnt[kRows][2];
-    constexpr int kWinBufs = 8 / KW;              // windows in flight per wave (8 KiB in all)
-    __shared__ __attribute__((aligned(1024))) float s_win[KW][kWinBufs][kWinFloats];
-    __shared__ float refs_l[kRows * kSplitMaxBps];                                   // block references
+    __shared__ unsigned s_cnt[kTR][2];
+    constexpr int kWinBufs = 2;                   // windows in flight per wave
+    __shared__ __attribute__((aligned(1024))) float s_win[NW][kWinBufs][kWinFloats];
+    __shared__ float refs_l[kTR * kMaxBps];                                          // block references
     extern __shared__ __attribute__((aligned(1024))) char ring[];
     const uint32_t ring_lds = (uint32_t)(uintptr_t)LDS_PTR(char, ring);
     const AttnParams& p = sp.a;
@@ -291,6 +346,7 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kw = wave % KW, bg0 = wave / KW;    // key slot and block group of this wave
     const int c16 = lane & 15;
     const int grp = lane >> 4;
     const int split = blockIdx.x % sp.nsplit;
@@ -309,9 +365,9 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     // -- block-maximum windows of the replay: a wave replays RPW rows at a
     //    time, L = 64/RPW lanes per row, and one wave-wide 1 KiB DMA brings the
     //    maxima of 4 L blocks of each of them
-    const int nr = min(kRows, flat - tile * kRows);         // rows of the tile (at least one)
-    const int rpw = nr <= KW ? 1 : (nr <= 2 * KW ? 2 : 4);
-    const int npass = (nr + KW * rpw - 1) / (KW * rpw);
+    const int nr = min(kTR, flat - tile * kTR);             // rows of the workgroup (at least one)
+    const int rpw = nr <= NW ? 1 : (nr <= 2 * NW ? 2 : 4);
+    const int npass = (nr + NW * rpw - 1) / (NW * rpw);
     const int wblk = kWinFloats / rpw;                       // blocks per window and row
     const int nwin = (j1 + wblk - 1) / wblk;
     const int nall = npass * nwin;                           // windows of this wave, pass by pass
@@ -319,7 +375,7 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     int ndma = 0;                                 // DMA ops of this wave issued so far
     {
         const uint32_t ctab_lds = (uint32_t)(uintptr_t)LDS_PTR(uint8_t, ctab);
-        for (int i = wave; i < kCodeTableBytes / 1024; i += KW) {
+        for (int i = wave; i < kCodeTableBytes / 1024; i += NW) {
             lds_dma_16(p.ctab + i * 1024 + 16 * lane, ctab_lds + (uint32_t)(i * 1024));
             ++ndma;
         }
@@ -327,39 +383,68 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     const int tagc = ndma;                        // ndma after this wave's part of the code table
     auto issue_win = [&](int i) {
         const int lpr = 64 / rpw;
-        const int srow = min((i / nwin * KW + wave) * rpw + lane / lpr, nr - 1);
-        const float* src = sp.bmax + (bg * flat + tile * kRows + srow) * sp.bstride + (i % nwin) * wblk + 4 * (lane % lpr);
+        const int srow = min((i / nwin * NW + wave) * rpw + lane / lpr, nr - 1);
+        const float* src = sp.bmax + (bg * flat + tile * kTR + srow) * sp.bstride + (i % nwin) * wblk + 4 * (lane % lpr);
         lds_dma_16(src, win_lds + (uint32_t)((i % kWinBufs) * 1024));
         ++ndma;
     };
     const int nearly = min(nall, kWinBufs);       // windows issued ahead of the V ring
     for (int i = 0; i < nearly; ++i) issue_win(i);
 
-    // -- the V ring of this split
+    // -- the ring of this wave (blocks bg0 + BG*i of the split): slot q holds
+    //    the raw dot products of run q / (kRun + 1) (q % (kRun + 1) == 0) or V
+    //    of one block of that run
+    const int mine = max(0, (nslots - bg0 + BG - 1) / BG);
+    const long long nkeys = (long long)sp.nblk * BLK;
+    const long long row0 = bg * flat + (long long)tile * kTR;    // the workgroup's first row
     const uint32_t my_ring_lds = ring_lds + (uint32_t)(wave * RW * C::kSlotBytes);
     const char* my_ring = ring + wave * RW * C::kSlotBytes;
-    auto issue_slot = [&](int n) {               // V keys [32*wave, +32) of block j0 + n
-        const int key0 = (j0 + n) * BLK + wave * kSlotKeys;
-        const uint32_t dst = my_ring_lds + (uint32_t)((n % RW) * C::kSlotBytes);
+    auto issue_slot = [&](int q) {               // keys [32*kw, +32) of the blocks
+        const int run = q / (kRun + 1), u = q % (kRun + 1);
+        const uint32_t dst = my_ring_lds + (uint32_t)((q % RW) * C::kSlotBytes);
+        if (u == 0) {
+            // 8 rows of 128 B per load; the 16-byte chunks of a row XOR-swizzled
 #pragma unroll
-        for (int t = 0; t < C::kIPS; ++t) {
-            const int rr = t * (1024 / C::kRowBytes) + lane / C::kCPR;
-            const int ch = (lane % C::kCPR) ^ v_swz<D>(rr);
-            const int key = min(key0 + rr, p.Sk - 1);
-            lds_dma_16(vbase + (long long)key * D + ch * 8, dst + t * 1024);
+            for (int t = 0; t < C::kIPS; ++t) {
+                if (run * kRun + t / (kTR / 8) >= mine) break;   // (the last run may hold fewer blocks)
+                const int n = bg0 + BG * (run * kRun + t / (kTR / 8));
+                const int rr = (t % (kTR / 8)) * 8 + lane / 8;
+                const int ch = (lane % 8) ^ (rr & 7);
+                lds_dma_16(sp.acc + (row0 + min(rr, nr - 1)) * nkeys + (j0 + n) * BLK + kw * kSlotKeys + 4 * ch,
+                           dst + t * 1024);
+                ++ndma;
+            }
+        } else {
+            const int key0 = (j0 + bg0 + BG * (run * kRun + u - 1)) * BLK + kw * kSlotKeys;
+#pragma unroll
+            for (int t = 0; t < C::kIPS; ++t) {
+                const int rr = t * (1024 / C::kRowBytes) + lane / C::kCPR;
+                const int ch = (lane % C::kCPR) ^ v_swz<D>(rr);
+                const int key = min(key0 + rr, p.Sk - 1);
+                lds_dma_16(vbase + (long long)key * D + ch * 8, dst + t * 1024);
+            }
+            ndma += C::kIPS;
         }
-        ndma += C::kIPS;
     };
+    const int nseq = mine + (mine + kRun - 1) / kRun;
+    // loads issued after slot q: kIPS per slot, fewer in the last run's dot products
+    const int last_a = ((mine + kRun - 1) / kRun - 1) * (kRun + 1);
+    const int short_by = C::kIPS - (mine - (mine - 1) / kRun * kRun) * (kTR / 8);
     int issued = 0;
-    for (; issued < min(nslots, RW); ++issued) issue_slot(issued);
+    for (; issued < min(nseq, RW); ++issued) issue_slot(issued);
 
     // -- the replay: Alg. 1's decision for every block of [0, j1) of a row, L
-    //    blocks (one per lane) evaluated per step at the current m; the blocks
-    //    up to the first one that changes m are settled, and the step repeats
-    //    from there with the new m.  It is a serial chain of short steps in
-    //    front of P V, so the rows of a tile share a wave's lanes instead of
-    //    taking turns: with one row per wave at a time, 6 queries of 4 heads on
-    //    3000 keys spent 23 of the kernel's 33 us here.
+    //    blocks (one per lane) per step.  The integer maximum is nearly always
+    //    the running maximum of the blocks' own ceil(row maximum): every lane
+    //    takes that as its guess of m before its block (a prefix maximum),
+    //    applies the rule of Alg. 1 to it, and the blocks up to the first one
+    //    whose result is not the next lane's guess are settled; the step
+    //    repeats from there with the true m.  This runs in front of P V, so it
+    //    is kept short: up to four rows share a wave where there are more rows
+    //    than waves (6 queries of 4 heads on 3000 keys, 4 sequences, kernel
+    //    time: 33 us with a row per wave at a time and a step per change of m,
+    //    18.8 us with four rows per wave, 11.4 us with eight waves and the
+    //    prefix maximum).
     const int tagv = ndma;                        // ndma after the V ring's first loads
     auto wait_win = [&](int i) { wait_vm(ndma - (i < nearly ? tagc + i + 1 : tagv + (i - nearly) + 1)); };
     const float* win = &s_win[wave][0][0];
@@ -368,9 +453,9 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
         constexpr int L = 64 / RPW, kWB = kWinFloats / RPW;
         const int sl = lane % L, sg = lane / L;   // this lane's block of the step, and its row
         for (int pass = 0; pass < npass; ++pass) {
-            const int srow = (pass * KW + wave) * RPW + sg;
+            const int srow = (pass * NW + wave) * RPW + sg;
             const bool row_ok = srow < nr;
-            const int last_blk = row_ok ? row_info(p, tile, g, srow).kmax / BLK : -1;   // B0 with b0_last
+            const int last_blk = row_ok ? row_info(p, tile * RT + srow / kRows, g, srow % kRows).kmax / BLK : -1;   // B0 with b0_last
             float m = ninf;
             unsigned n_restart = 0, n_visit = 0;
             for (int w = 0; w < nwin; ++w) {
@@ -387,37 +472,35 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
                     const bool vis = amax != ninf;
                     const float ceil_ac = ceilf(amax * c);
                     const bool in_b0 = jb < p.n_b0 || (p.b0_last && jb == last_blk);
-                    const bool mine = row_ok && jb >= j0 && jb < j1;
+                    const bool in_split = row_ok && jb >= j0 && jb < j1;
+                    const float h = vis ? ceil_ac : ninf;
                     int lo = 0;
                     for (;;) {
                         // (the restart test and the increment as in the
                         // prefill kernel: lambda <= kCodeMaxLambda here)
-                        const bool forced = in_b0 || (m == ninf);
-                        const float xt = __builtin_fmaf(amax, c, -m);
+                        const float g = __builtin_fmaxf(m, prefix_max_before<L>(sl >= lo ? h : ninf));
+                        const bool forced = in_b0 || (g == ninf);
+                        const float xt = __builtin_fmaf(amax, c, -g);
                         const bool restart = forced || (xt >= p.dec_x0);
-                        const float m_hi = __builtin_fmaxf(m, ceil_ac);
-                        const float m_new = vis ? (restart ? m_hi : m + hif8_ceil_below9(xt)) : m;
-                        const float ref_new = vis ? (restart ? m_hi : m) : ninf;
+                        const float m_hi = __builtin_fmaxf(g, ceil_ac);
+                        const float m_new = vis ? (restart ? m_hi : g + hif8_ceil_below9(xt)) : g;
+                        const float ref_new = vis ? (restart ? m_hi : g) : ninf;
                         const bool pend = sl >= lo;
-                        const unsigned long long bal = __ballot(pend && hif8::f2u(m_new) != hif8::f2u(m));
-                        const unsigned long long mine_bal = RPW == 1 ? bal : (bal >> (sg * L)) & ((1ull << (L & 63)) - 1);
-                        const int f = mine_bal ? (int)__builtin_ctzll(mine_bal) : L;   // this row's first change of m
-                        if (pend && sl <= f && mine) {
-                            refs_l[srow * kSplitMaxBps + (jb - j0)] = ref_new;   // -inf: no visible key
+                        const unsigned long long bal = __ballot(pend && m_new != __builtin_fmaxf(g, h));
+                        const unsigned long long gb = RPW == 1 ? bal : (bal >> (sg * L)) & ((1ull << (L & 63)) - 1);
+                        const int f = gb ? (int)__builtin_ctzll(gb) : L - 1;   // this row's last settled block
+                        if (pend && sl <= f && in_split) {
+                            refs_l[srow * kMaxBps + (jb - j0)] = ref_new;   // -inf: no visible key
                             const bool b1 = vis && !in_b0;
                             n_visit += b1 ? 1u : 0u;
                             n_restart += (b1 && restart) ? 1u : 0u;
                         }
-                        if constexpr (RPW == 1) {             // (wave-uniform: a scalar register)
-                            if (f < 64) m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(
-                                                __builtin_bit_cast(int, m_new), f & 63));
-                            if (f >= 63) break;
-                        } else {
-                            const float at = __shfl(m_new, sg * L + min(f, L - 1), 64);
-                            m = f < L ? at : m;
-                            if (!__any(f < L - 1)) break;
-                        }
+                        // (a row whose step is done has lo = L: its lanes hold
+                        // g = m, and m stays)
+                        const float at = __shfl(m_new, sg * L + f, 64);
+                        m = lo < L ? at : m;
                         lo = f + 1;
+                        if (!__any(lo < L)) break;
                     }
                 }
                 if (i + kWinBufs < nall) issue_win(i + kWinBufs);
@@ -438,14 +521,18 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     else replay(std::integral_constant<int, 4>{});
     wait_vm(ndma - tagc);                         // this wave's part of the code table has landed
 
-    const RowInfo ri = row_info(p, tile, g, c16);
-    const long long nkeys = (long long)sp.nblk * BLK;
-    const long long rowoff = bg * flat + (ri.ok ? ri.f : 0);
-    const float* acc_row = sp.acc + rowoff * nkeys;
-    float cur = ninf, dl = 0.0f;                  // X and dX are relative to the reference cur
-    f32x4 oacc[kDT];
+    bool ok[RT];
 #pragma unroll
-    for (int t = 0; t < kDT; ++t) oacc[t] = f32x4{};
+    for (int rt = 0; rt < RT; ++rt) ok[rt] = rt * kRows + c16 < nr;
+    float cur[RT], dl[RT];                        // X and dX are relative to the reference cur
+    f32x4 oacc[RT][kDT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        cur[rt] = ninf;
+        dl[rt] = 0.0f;
+#pragma unroll
+        for (int t = 0; t < kDT; ++t) oacc[rt][t] = f32x4{};
+    }
     const int vrow0 = 4 * grp + c16 / 4;
     const int vx = v_swz<D>(vrow0);
     const int vd0 = 4 * (c16 & 3);
@@ -453,110 +540,144 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
     __syncthreads();                              // code table, references and counts published
 
-    // The raw dot products of kAccRun blocks are loaded together at the start
-    // of each run of blocks: the first use of a load waits for every older
-    // memory operation of the wave, which includes the V ring's loads in
-    // flight, so one load per block would let only one slot of the ring fly.
-    constexpr int kAccRun = 4;
-    for (int n0 = 0; n0 < nslots; n0 += kAccRun) {
-    f32x4 accr[kAccRun][2];
+    int q = 0;                                    // ring slot to consume next
+    auto wait_slot = [&]() {
+        wait_vm((issued - 1 - q) * C::kIPS - (q < last_a && last_a < issued ? short_by : 0));
+    };
+    auto next_slot = [&]() {
+        if (issued < nseq) { issue_slot(issued); ++issued; }
+        ++q;
+    };
+    for (int n0 = 0; n0 < mine; n0 += kRun) {
+        // P of the run's blocks from their dot products and references (the
+        // partials follow the references with exact rescales), all ahead of
+        // their P V: the dot products landed in front of V, so this overlaps
+        // V's way from memory
+        float fac[kRun][RT];
+        u32x4 pop[kRun][RT];
+        wait_slot();
+        const char* aslot = my_ring + (q % RW) * C::kSlotBytes;
 #pragma unroll
-    for (int u = 0; u < kAccRun; ++u) {
-        const int key0 = (j0 + n0 + u) * BLK + wave * kSlotKeys;
+        for (int u = 0; u < kRun; ++u) {
+            if (n0 + u >= mine) break;
 #pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2)
-            accr[u][t2] = (ri.ok && n0 + u < nslots) ? *reinterpret_cast<const f32x4*>(acc_row + key0 + 16 * t2 + 4 * grp)
-                                                     : f32x4{ninf, ninf, ninf, ninf};
-    }
+            for (int rt = 0; rt < RT; ++rt) {
+                const int row = rt * kRows + c16;
+                const float rj = ok[rt] ? refs_l[row * kMaxBps + bg0 + BG * (n0 + u)] : ninf;
+                fac[u][rt] = (cur[rt] == ninf || rj == ninf) ? 1.0f : exp2_int(cur[rt] - rj);
+                dl[rt] *= fac[u][rt];
+                if (rj != ninf) cur[rt] = rj;
+                const float nref = (cur[rt] == ninf) ? 0.0f : -cur[rt];
+                f32x4 sacc[2];
 #pragma unroll
-    for (int u = 0; u < kAccRun; ++u) {
-        const int n = n0 + u;
-        if (n >= nslots) break;
-        const int jb = j0 + n;
-        const int key0 = jb * BLK + wave * kSlotKeys;
-        // this block's reference; the partials follow it with exact rescales
-        const float rj = ri.ok ? refs_l[c16 * kSplitMaxBps + n] : ninf;
-        const float fac = (cur == ninf || rj == ninf) ? 1.0f : exp2_int(cur - rj);
-        if (__any(fac != 1.0f)) {
+                for (int t2 = 0; t2 < 2; ++t2) {
+                    sacc[t2] = *reinterpret_cast<const f32x4*>(aslot + u * kAccBytes + row * 128 + 16 * ((4 * t2 + grp) ^ (row & 7)));
+                    if (!ok[rt]) sacc[t2] = f32x4{ninf, ninf, ninf, ninf};
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int t2 = e >> 1;
+                    const float t0 = __builtin_fmaf(sacc[t2][2 * (e & 1)], c, nref);
+                    const float t1 = __builtin_fmaf(sacc[t2][2 * (e & 1) + 1], c, nref);
+                    const uint32_t i0 = min(max(hif8::f2u(t0) >> kTabShift, (uint32_t)kCodeLo), (uint32_t)kCodeHi);
+                    const uint32_t i1 = min(max(hif8::f2u(t1) >> kTabShift, (uint32_t)kCodeLo), (uint32_t)kCodeHi);
+                    const uint32_t w = ((uint32_t)ctab[i0 - kCodeLo] | ((uint32_t)ctab[i1 - kCodeLo] << 16)) << 4;
+                    pop[u][rt][e] = w;
+                    dl[rt] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, dl[rt], false);
+                }
+            }
+        }
+        asm volatile("" ::: "memory");            // (the slot is read before it is filled again)
+        next_slot();
+#pragma unroll
+        for (int u = 0; u < kRun; ++u) {
+            if (n0 + u >= mine) break;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+                if (__any(fac[u][rt] != 1.0f)) {
+#pragma unroll
+                    for (int t = 0; t < kDT; ++t)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) oacc[rt][t][i] *= fac[u][rt];
+                }
+            wait_slot();
+            const char* slot = my_ring + (q % RW) * C::kSlotBytes;
+            // (every operand read of the block ahead of its MFMAs)
+            u32x4 va[kDT];
+#pragma unroll
+            for (int t = 0; t < kDT; ++t) {
+                const char* pa = slot + vrow + 16 * (((16 * t + vd0) >> 3) ^ vx);
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, pa));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, pa + 16 * C::kRowBytes));
+                va[t] = u32x4{__builtin_bit_cast(u32x2, lo)[0], __builtin_bit_cast(u32x2, lo)[1],
+                              __builtin_bit_cast(u32x2, hi)[0], __builtin_bit_cast(u32x2, hi)[1]};
+            }
 #pragma unroll
             for (int t = 0; t < kDT; ++t)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) oacc[t][i] *= fac;
+                for (int rt = 0; rt < RT; ++rt)
+                    oacc[rt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(va[t]), as_bf16x8(pop[u][rt]), oacc[rt][t], 0, 0, 0);
+            next_slot();
         }
-        dl *= fac;
-        if (rj != ninf) cur = rj;
-        const float nref = (cur == ninf) ? 0.0f : -cur;
-        const f32x4* sacc = accr[u];
-        u32x4 pop;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int t2 = e >> 1;
-            const float t0 = __builtin_fmaf(sacc[t2][2 * (e & 1)], c, nref);
-            const float t1 = __builtin_fmaf(sacc[t2][2 * (e & 1) + 1], c, nref);
-            const uint32_t i0 = min(max(hif8::f2u(t0) >> kTabShift, (uint32_t)kCodeLo), (uint32_t)kCodeHi);
-            const uint32_t i1 = min(max(hif8::f2u(t1) >> kTabShift, (uint32_t)kCodeLo), (uint32_t)kCodeHi);
-            const uint32_t w = ((uint32_t)ctab[i0 - kCodeLo] | ((uint32_t)ctab[i1 - kCodeLo] << 16)) << 4;
-            pop[e] = w;
-            dl = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, dl, false);
-        }
-        wait_vm((issued - 1 - n) * C::kIPS);
-        const char* slot = my_ring + (n % RW) * C::kSlotBytes;
-#pragma unroll
-        for (int t = 0; t < kDT; ++t) {
-            const char* pa = slot + vrow + 16 * (((16 * t + vd0) >> 3) ^ vx);
-            const s16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, pa));
-            const s16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, pa + 16 * C::kRowBytes));
-            const u32x4 a = {__builtin_bit_cast(u32x2, va)[0], __builtin_bit_cast(u32x2, va)[1],
-                             __builtin_bit_cast(u32x2, vb)[0], __builtin_bit_cast(u32x2, vb)[1]};
-            oacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(pop), oacc[t], 0, 0, 0);
-        }
-        if (issued < nslots) { issue_slot(issued); ++issued; }
-    }
     }
 
-    // -- one sum over the waves (they share the references), then this
-    //    split's part: X, dX and the reference cur they are relative to
-    float dw = dl + __shfl_xor(dl, 16, 64);
-    dw += __shfl_xor(dw, 32, 64);
-    if constexpr (KW > 1) {
-        float* mb = reinterpret_cast<float*>(ring);             // [KW-1][kRows][D]
-        float* db = mb + (KW - 1) * kRows * D;                  // [KW-1][kRows]
-        __syncthreads();
-        if (wave > 0) {
-            float* mine = mb + (wave - 1) * kRows * D + c16 * D;
+    // -- one sum over the waves through the ring (chunks of 4 values of d
+    //    swizzled by row), the block groups brought to the latest reference of
+    //    the row; this split's partial: X, dX and that reference
+    constexpr int QD = D / 4;                     // chunks per row
+    static_assert(C::kLdsBytes >= NW * kTR * D * 4, "merge buffer fits the ring");
+    static_assert(sizeof(float) * (NW + BG) * kTR <= sizeof(s_win), "denominators and references fit the windows");
+    f32x4* mb = reinterpret_cast<f32x4*>(ring);                  // [NW][kTR][QD]
+    float* db = &s_win[0][0][0];                                 // [NW][kTR], then the references [BG][kTR]
+    float* rb = db + NW * kTR;
+    __syncthreads();
 #pragma unroll
-            for (int t = 0; t < kDT; ++t) *reinterpret_cast<f32x4*>(mine + 16 * t + 4 * grp) = oacc[t];
-            if (grp == 0) db[(wave - 1) * kRows + c16] = dw;
-        }
-        __syncthreads();
-        if (wave == 0) {
+    for (int rt = 0; rt < RT; ++rt) {
+        const int row = rt * kRows + c16;
+#pragma unroll
+        for (int t = 0; t < kDT; ++t) mb[(wave * kTR + row) * QD + ((4 * t + grp) ^ (c16 & (QD - 1)))] = oacc[rt][t];
+        float dw = dl[rt] + __shfl_xor(dl[rt], 16, 64);
+        dw += __shfl_xor(dw, 32, 64);
+        if (grp == 0) db[wave * kTR + row] = dw;
+        if (grp == 0 && kw == 0) rb[bg0 * kTR + row] = cur[rt];
+    }
+    __syncthreads();
+    float* prow0 = sp.part + split * ((long long)p.B * p.Hkv * flat * PS) + row0 * PS;
+    for (int i = tid; i < nr * QD; i += NT) {
+        const int row = i / QD, ch = i % QD;
+        float top = rb[row];
+#pragma unroll
+        for (int g2 = 1; g2 < BG; ++g2) top = __builtin_fmaxf(top, rb[g2 * kTR + row]);
+        f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+        float d = 0.0f;
+#pragma unroll
+        for (int g2 = 0; g2 < BG; ++g2) {
+            f32x4 y = mb[(g2 * KW * kTR + row) * QD + (ch ^ (row & 15 & (QD - 1)))];
+            float e1 = db[g2 * KW * kTR + row];
 #pragma unroll
             for (int w = 1; w < KW; ++w) {
-                const float* theirs = mb + (w - 1) * kRows * D + c16 * D;
+                const f32x4 z = mb[((g2 * KW + w) * kTR + row) * QD + (ch ^ (row & 15 & (QD - 1)))];
 #pragma unroll
-                for (int t = 0; t < kDT; ++t) {
-                    const f32x4 v = *reinterpret_cast<const f32x4*>(theirs + 16 * t + 4 * grp);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) oacc[t][e] += v[e];
-                }
-                dw += db[(w - 1) * kRows + c16];
+                for (int e = 0; e < 4; ++e) y[e] += z[e];
+                e1 += db[(g2 * KW + w) * kTR + row];
             }
-        }
-    }
-    const long long rows_all = (long long)p.B * p.Hkv * flat;
-    if (wave == 0 && ri.ok) {
-        float* prow = sp.part + ((long long)split * rows_all + rowoff) * PS;
+            // (a group that saw no key adds nothing)
+            const float rg = rb[g2 * kTR + row];
+            const float f = rg == ninf ? 0.0f : exp2_int(rg - top);
 #pragma unroll
-        for (int t = 0; t < kDT; ++t) *reinterpret_cast<f32x4*>(prow + 16 * t + 4 * grp) = oacc[t];
-        if (grp == 0) {
-            prow[D] = dw;
-            prow[D + 1] = cur;
+            for (int e = 0; e < 4; ++e) x[e] += f * y[e];
+            d += f * e1;
+        }
+        *reinterpret_cast<f32x4*>(prow0 + row * PS + 4 * ch) = x;
+        if (ch == 0) {
+            prow0[row * PS + D] = d;
+            prow0[row * PS + D + 1] = top;
         }
     }
     // restart counters of this split's blocks (a tile is one row here)
-    if (tid < kRows) {
-        const RowInfo cr = row_info(p, tile, g, tid);
-        if (cr.ok && s_cnt[tid][1]) {
+    if (tid < nr) {
+        const RowInfo cr = row_info(p, tile * RT + tid / kRows, g, tid % kRows);
+        if (s_cnt[tid][1]) {
             if (p.counters) {
                 unsigned long long* cp = p.counters + 2 * ((long long)b * p.Hq + cr.h);
                 atomicAdd(cp + 0, (unsigned long long)s_cnt[tid][0]);
@@ -570,7 +691,6 @@ __global__ __launch_bounds__(64 * (BLK / 32)) void split_pv_kernel(SplitParams s
         }
     }
 }
-
 
 // ---------------------------------------------------------------------------
 // 3. combine: one workgroup per row; groups of threads take every SG-th split
@@ -665,47 +785,65 @@ __global__ __launch_bounds__(256) void split_combine_kernel(SplitParams sp)
             empty ? ninf : 0.69314718055994531f * (rr + (log2f(dx) + (float)kCodeBiasLog2));
 }
 
-template <int D, int BLK>
-hipError_t launch_split_db(const SplitParams& sp, hipStream_t st)
+template <int D, int BLK, int RT, bool BIG>
+hipError_t launch_split_big(const SplitParams& sp, hipStream_t st)
 {
-    using C = SCfg<D, BLK>;
-    using PC = PCfg<D, BLK>;
-    static_assert(C::kLdsBytes >= (C::kWaves - 1) * kRows * (D + 1) * 4, "merge buffer fits the ring");
+    using C = SCfg<D, BLK, BIG>;
     static DeviceOnce attr_set;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (!attr_set.is_done(dev)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, false>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&split_pv_kernel<D, BLK>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, PC::kLdsBytes);
-        if (e != hipSuccess) return e;
+        const void* fns[] = {reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, false, RT, BIG>),
+                             reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, true, RT, BIG>),
+                             reinterpret_cast<const void*>(&split_pv_kernel<D, BLK, RT, BIG>)};
+        for (const void* fn : fns) {
+            e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
+            if (e != hipSuccess) return e;
+        }
         attr_set.mark(dev);
     }
     const AttnParams& p = sp.a;
-    if (sp.bps < 1 || sp.bps > kSplitMaxBps || sp.bstride % kWinFloats || sp.bstride < sp.nblk ||
-        (long long)sp.nsplit * sp.bps < sp.nblk || (long long)(sp.nsplit - 1) * sp.bps >= sp.nblk)
-        return hipErrorInvalidValue;
     const long long flat = (long long)p.Sq * (p.Hq / p.Hkv);
-    const unsigned tiles = (unsigned)((flat + kRows - 1) / kRows);
-    const dim3 grid(tiles * (unsigned)sp.nsplit, (unsigned)p.Hkv, (unsigned)p.B);
-    if (p.qk_f8)
-        hipLaunchKernelGGL((split_scores_kernel<D, BLK, true>), grid, dim3(64 * C::kWaves), C::kLdsBytes, st, sp);
-    else
-        hipLaunchKernelGGL((split_scores_kernel<D, BLK, false>), grid, dim3(64 * C::kWaves), C::kLdsBytes, st, sp);
+    const unsigned tiles = (unsigned)((flat + RT * kRows - 1) / (RT * kRows));
+    const dim3 grid(tiles * (unsigned)sp.nsplit, (unsigned)p.Hkv, (unsigned)p.B), block(64 * C::kWaves);
+    if (p.qk_f8) hipLaunchKernelGGL((split_scores_kernel<D, BLK, true, RT, BIG>), grid, block, C::kLdsBytes, st, sp);
+    else hipLaunchKernelGGL((split_scores_kernel<D, BLK, false, RT, BIG>), grid, block, C::kLdsBytes, st, sp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((split_pv_kernel<D, BLK>), grid, dim3(PC::kThreads), PC::kLdsBytes, st, sp);
+    hipLaunchKernelGGL((split_pv_kernel<D, BLK, RT, BIG>), grid, block, C::kLdsBytes, st, sp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((split_combine_kernel<D>), dim3((unsigned)flat, (unsigned)p.Hkv, (unsigned)p.B), dim3(256), 0,
                        st, sp);
     return hipGetLastError();
+}
+
+template <int D, int BLK, int RT>
+hipError_t launch_split_rt(const SplitParams& sp, hipStream_t st)
+{
+    int ncu = 0;
+    const hipError_t e = cu_count(&ncu);
+    if (e != hipSuccess) return e;
+    const AttnParams& p = sp.a;
+    const long long flat = (long long)p.Sq * (p.Hq / p.Hkv);
+    const long long wgs = (flat + RT * kRows - 1) / (RT * kRows) * sp.nsplit * p.Hkv * p.B;
+    return wgs <= ncu ? launch_split_big<D, BLK, RT, true>(sp, st) : launch_split_big<D, BLK, RT, false>(sp, st);
+}
+
+template <int D, int BLK>
+hipError_t launch_split_db(const SplitParams& sp, hipStream_t st)
+{
+    const AttnParams& p = sp.a;
+    if (sp.bps < 1 || sp.bps > kSplitMaxBps || sp.bstride % kWinFloats || sp.bstride < sp.nblk ||
+        (long long)sp.nsplit * sp.bps < sp.nblk || (long long)(sp.nsplit - 1) * sp.bps >= sp.nblk)
+        return hipErrorInvalidValue;
+    // more than 16 rows per key/value head: 32 per workgroup, so that K and V
+    // are streamed once for both tiles (8 sequences, 32 rows, 4000 keys: scores
+    // 31.7 -> 20.9 us, pv 36.6 -> 23.5 us); the references of the split's
+    // blocks then fit in LDS up to 16 blocks
+    if ((long long)p.Sq * (p.Hq / p.Hkv) > kRows && sp.bps <= kSplitMaxBps / 2) return launch_split_rt<D, BLK, 2>(sp, st);
+    return launch_split_rt<D, BLK, 1>(sp, st);
 }
 
 }  // namespace
