@@ -199,7 +199,7 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 // every T has it: ceil(HiF8(.)) does not decrease with T, so a binary search
 // over the fp32 values in order finds the step.  Alg. 1 restarts a block in
 // B1 exactly when the 8-bit T of its row maximum reaches it.
-float restart_threshold(int lambda)
+float find_restart_threshold(int lambda)
 {
     auto key_value = [](uint32_t key) {              // key order = value order over all non-NaN fp32
         const uint32_t bits = (key & 0x80000000u) ? (key & 0x7fffffffu) : ~key;
@@ -216,6 +216,16 @@ float restart_threshold(int lambda)
     return key_value(hi);
 }
 
+// The same; the thresholds in use (0 to 8) are searched once.
+float restart_threshold(int lambda)
+{
+    struct Kept {
+        float t[kCodeMaxLambda + 1];
+        Kept() { for (int i = 0; i <= kCodeMaxLambda; ++i) t[i] = find_restart_threshold(i); }
+    };
+    static const Kept kept;
+    return lambda >= 0 && lambda <= kCodeMaxLambda ? kept.t[lambda] : find_restart_threshold(lambda);
+}
 
 // Canonical knobs when the caller passes none.
 baps_params_t knobs_of(const baps_params_t* prm)

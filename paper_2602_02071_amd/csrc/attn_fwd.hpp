@@ -978,7 +978,7 @@ hipError_t launch_one(const AttnParams& p, hipStream_t st)
         reinterpret_cast<const void*>(&baps_attn_fwd_kernel<D, BLK, NW, KW, CT, MODE, TILE, F8, kPersist, TIE, DUMP>);
     int dev = 0, ncu = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) e = cu_count(&ncu);
     if (e != hipSuccess) return e;
     // resident workgroups per CU, found once per device ordinal below 64
     // (the kernel's resources do not depend on the call; 0: not yet found)
