@@ -21,7 +21,9 @@ HIPCC_FLAGS = [
 # per-source extra flags.  The fused attention kernel takes finite scores (or
 # -inf for masked keys) only, so its max reductions need no NaN quieting.
 EXTRA_FLAGS = {"attn_fwd.hip": ["-fno-honor-nans"], "attn_fwd_dump.hip": ["-fno-honor-nans"],
-               "attn_decode.hip": ["-fno-honor-nans"], "softmax_block.hip": ["-fno-honor-nans"]}
+               "attn_decode.hip": ["-fno-honor-nans"],
+               # the encoder's tables are evaluated at compile time
+               "codec.hip": ["-fconstexpr-steps=100000000"], "softmax_block.hip": ["-fno-honor-nans"]}
 
 
 def sources():

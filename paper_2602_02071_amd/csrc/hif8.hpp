@@ -17,9 +17,9 @@
 #include <stdint.h>
 
 #if defined(__HIPCC__)
-#define HIF8_HD __host__ __device__ __forceinline__
+#define HIF8_HD __host__ __device__ __forceinline__ constexpr
 #else
-#define HIF8_HD inline
+#define HIF8_HD inline constexpr
 #endif
 
 namespace hif8 {
