@@ -15,7 +15,7 @@ using namespace baps;
 // i.  P = HiF8(2^HiF8(T)) (App. A: the power of two evaluated on the 8-bit
 // input and rounded back to 8 bits), as fp32 bits with the HiF8 code of P
 // in the low byte.  Lives in static device memory, one copy per device.
-__device__ uint32_t g_score_table[kTabEntries];
+__device__ __attribute__((aligned(16))) uint32_t g_score_table[kTabEntries];
 // The compact code table of the fused attention kernels (see common.hpp).
 __device__ __attribute__((aligned(256))) uint8_t g_code_table[kCodeTableBytes];
 // The same table expanded to every score-table index (indices below kCodeLo

@@ -295,27 +295,6 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void split_scores_kernel(SplitP
 // ---------------------------------------------------------------------------
 constexpr int kWinFloats = 256;      // block maxima per LDS window of the replay
 
-// Lanes in groups of L (16, 32 or 64): the maximum of v over the lower lanes of
-// the group, -inf for its first lane
-template <int L>
-__device__ __forceinline__ float prefix_max_before(float v)
-{
-    const float ninf = -__builtin_huge_valf();
-    const int ni = __builtin_bit_cast(int, ninf);
-#define BAPS_STEP(CTRL, ROWS)                                                                                     \
-    v = __builtin_fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(ni, __builtin_bit_cast(int, v),  \
-                                                                                 CTRL, ROWS, 0xF, false)))
-    BAPS_STEP(0x111, 0xF);                        // row_shr 1, 2, 4, 8: inclusive maxima within 16 lanes
-    BAPS_STEP(0x112, 0xF);
-    BAPS_STEP(0x114, 0xF);
-    BAPS_STEP(0x118, 0xF);
-    if constexpr (L >= 32) BAPS_STEP(0x142, 0xA);   // lane 15 of rows 0 and 2 to rows 1 and 3
-    if constexpr (L == 64) BAPS_STEP(0x143, 0xC);   // lane 31 to rows 2 and 3
-#undef BAPS_STEP
-    const float before = __shfl_up(v, 1, 64);
-    return (threadIdx.x & (L - 1)) == 0 ? ninf : before;
-}
-
 // RT tiles of 16 rows per workgroup share every V (and, in the scores pass, K) read.
 template <int D, int BLK, int RT, bool BIG>
 __global__ __launch_bounds__(BIG ? 512 : 256, 2) void split_pv_kernel(SplitParams sp)

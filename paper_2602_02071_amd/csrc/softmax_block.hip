@@ -280,6 +280,221 @@ __global__ __launch_bounds__(NT) void softmax_block4_kernel(SoftmaxBlockParams p
     }
 }
 
+// Wide form: a workgroup of 256 threads takes whole rows, 4096 columns at a
+// time with the next chunk's loads in flight.  The rule of Alg. 1
+// depends on a block only through its maximum, so per chunk the maxima of
+// every 64 columns meet in LDS (the only barrier), every wave runs the rule
+// over the chunk's blocks, one per lane, and then all threads form their codes
+// at the references found.  The rule itself is serial, but the integer maximum
+// is nearly always the running maximum of the blocks' own ceil(maximum): each
+// lane takes that as its guess (a prefix maximum), the blocks up to the first
+// one whose result is not the next lane's guess are settled, and the step
+// repeats from there.  A thread sums its P relative to the latest integer
+// maximum by exact powers of two.  VEC: 16-byte aligned rows of a multiple of
+// 4 columns (4 adjacent columns per lane); else columns go lane by lane.
+//
+// The other kernels give a row 16 or 64 lanes and walk it in steps: with few
+// rows that walk, not memory, is the time (300 rows of 30000 columns 158 us,
+// here 22; 4096 x 4096 41 -> 20 us; 16384 x 8192 142 -> 126 us, 5.5 TB/s).
+constexpr int kWideMaxBlk = 1024;                 // blocks per row (their references stay in LDS)
+
+template <int BLOCK, bool VEC>
+__global__ __launch_bounds__(kThreads) void softmax_block_wide_kernel(SoftmaxBlockParams p)
+{
+    constexpr int NT = kThreads;
+    constexpr int kCols = 16 * NT;                        // columns per chunk
+    constexpr int kSub = kCols / 64;                      // 64-column pieces per chunk
+    constexpr int kNB = kCols / BLOCK;                    // blocks per chunk
+    constexpr int kSteps = (kNB + 63) / 64;
+    __shared__ __attribute__((aligned(16))) uint32_t tab[kTabEntries];
+    __shared__ float maxs[2][kSub];
+    __shared__ float refs_l[kWideMaxBlk];
+    __shared__ float wsum[NT / 64];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = 4 * tid; i < kTabEntries; i += 4 * NT)
+        *reinterpret_cast<u32x4*>(tab + i) = *reinterpret_cast<const u32x4*>(p.tab + i);
+
+    const long long cols = p.cols;
+    const int nblk = (int)((cols + BLOCK - 1) / BLOCK);
+    const int nchunk = (int)((cols + kCols - 1) / kCols);
+    const float ninf = -__builtin_huge_valf();
+    // column of element (u, e) of this thread in a chunk
+    auto col = [&](int u, int e) { return VEC ? u * 4 * NT + 4 * tid + e : (4 * u + e) * NT + tid; };
+    auto load = [&](f32x4* v, const float* S, long long c0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if constexpr (VEC) {
+                const long long c = c0 + col(u, 0);
+                v[u] = c < cols ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(S + c))
+                                : f32x4{ninf, ninf, ninf, ninf};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const long long c = c0 + col(u, e);
+                    v[u][e] = c < cols ? __builtin_nontemporal_load(S + c) : ninf;
+                }
+            }
+        }
+    };
+    int par = 0;                                          // buffer of maxs
+    for (long long row = blockIdx.x; row < p.rows; row += gridDim.x) {
+        const float* S = p.s + row * p.ld;
+        uint8_t* code = p.codes + row * cols;
+        float m = ninf, dl = 0.0f;
+        f32x4 cur[4], nxt[4];
+        load(cur, S, 0);
+        for (int ch = 0; ch < nchunk; ++ch, par ^= 1) {
+            const long long c0 = (long long)ch * kCols;
+            if (ch + 1 < nchunk) load(nxt, S, c0 + kCols);
+            // maxima of the 64-column pieces
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (VEC) {
+                    const float mx = row16_max(fmaxf(fmaxf(cur[u][0], cur[u][1]), fmaxf(cur[u][2], cur[u][3])));
+                    if ((lane & 15) == 0) maxs[par][u * (NT / 16) + (tid >> 4)] = mx;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float mx = wave_max_uniform(cur[u][e]);
+                        if (lane == 0) maxs[par][(4 * u + e) * (NT / 64) + wave] = mx;
+                    }
+                }
+            }
+            __syncthreads();                              // (and, the first time, the table)
+            // the rule over the chunk's blocks
+            float refs[kSteps];
+            const float m_old = m;
+#pragma unroll
+            for (int st = 0; st < kSteps; ++st) {
+                const int jl = 64 * st + lane;            // block of the chunk, and of the row
+                const int j = ch * kNB + jl;
+                float M = ninf;
+                if (jl < kNB) {
+#pragma unroll
+                    for (int k = 0; k < BLOCK / 64; ++k) M = fmaxf(M, maxs[par][jl * (BLOCK / 64) + k]);
+                }
+                const bool in_row = jl < kNB && j < nblk;
+                const float h = in_row ? ceilf(M) : ninf;
+                float ref = ninf;
+                bool rst = false;
+                int lo = 0;
+                for (;;) {
+                    const float g = fmaxf(m, prefix_max_before<64>(lane >= lo ? h : ninf));
+                    float tq = ninf;
+                    if (M != ninf) tq = hif8::round(M - g);       // g = -inf gives +inf: restart
+                    const bool restart = j < p.n_b0 || ceilf(tq) > (float)p.lambda;
+                    const float m_new = !in_row ? g : (restart ? fmaxf(g, h) : g + fmaxf(0.0f, ceilf(tq)));
+                    const bool pend = lane >= lo;
+                    const unsigned long long bal = __ballot(pend && m_new != fmaxf(g, h));
+                    const int f = bal ? (int)__builtin_ctzll(bal) : 63;
+                    if (pend && lane <= f) {
+                        ref = restart ? m_new : g;
+                        rst = restart;
+                    }
+                    m = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, m_new), f));
+                    lo = f + 1;
+                    if (lo > 63) break;
+                }
+                refs[st] = ref;
+                if (wave == 0 && in_row) {
+                    refs_l[j] = ref;
+                    if (p.restarted) p.restarted[row * nblk + j] = rst ? 1 : 0;
+                }
+            }
+            // codes, and this thread's P relative to the new integer maximum
+            dl = (m_old == ninf) ? 0.0f : dl * exp2_int(m_old - m);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                uint32_t word = 0;
+                float rowsum = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // (VEC: the four columns share a block; else each column of the wave does)
+                    const int base = VEC ? u * 4 * NT : (4 * u + e) * NT;
+                    const int st = (base / BLOCK) / 64;
+                    const int src = VEC ? (base / BLOCK) % 64 + (BLOCK <= 4 * NT ? 4 * tid / BLOCK : 0)
+                                        : (base + 64 * wave) / BLOCK - 64 * st;
+                    float ref, beta;
+                    if constexpr (VEC) ref = __shfl(refs[st], src, 64);
+                    else ref = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, refs[st]), src));
+                    const float sv = cur[u][e];
+                    const float T = (sv == ninf || ref == ninf) ? ninf : sv - ref;
+                    const uint32_t ent = tab[hif8::f2u(T) >> kTabShift];
+                    const float pv = hif8::u2f(ent & 0xffffff00u);
+                    if constexpr (VEC) {
+                        word |= (ent & 0xffu) << (8 * e);
+                        rowsum += pv;
+                        if (e == 3) {
+                            beta = (ref == ninf) ? 0.0f : exp2_int(ref - m);
+                            dl += beta * rowsum;
+                            const long long c = c0 + col(u, 0);
+                            if (c < cols) *reinterpret_cast<uint32_t*>(code + c) = word;
+                        }
+                    } else {
+                        beta = (ref == ninf) ? 0.0f : exp2_int(ref - m);
+                        dl += beta * pv;
+                        const long long c = c0 + col(u, e);
+                        if (c < cols) code[c] = (uint8_t)(ent & 0xffu);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+        }
+        const float ws = wave_sum(dl);
+        if (lane == 0) wsum[wave] = ws;
+        __syncthreads();                                  // references and sums of the row
+        if (tid == 0) {
+            float d = wsum[0];
+#pragma unroll
+            for (int w = 1; w < NT / 64; ++w) d += wsum[w];
+            p.m_final[row] = m;
+            p.d_final[row] = d;
+        }
+        for (int idx = tid; idx < nblk; idx += NT) {
+            const float ref = refs_l[idx];
+            p.ref_shift[row * nblk + idx] =
+                (ref == ninf || m == ninf) ? INT32_MIN : (int32_t)fmaxf(ref - m, -2147483520.0f);
+        }
+        __syncthreads();                                  // read before the next row writes
+    }
+}
+
+template <bool VEC>
+hipError_t launch_wide(const SoftmaxBlockParams& p, int ncu, hipStream_t st)
+{
+    const long long most = 4LL * ncu;                     // 37 KiB of LDS: four workgroups per CU
+    const dim3 grid((unsigned)(p.rows < most ? p.rows : most));
+    switch (p.block) {
+    case 64: hipLaunchKernelGGL((softmax_block_wide_kernel<64, VEC>), grid, dim3(kThreads), 0, st, p); break;
+    case 128: hipLaunchKernelGGL((softmax_block_wide_kernel<128, VEC>), grid, dim3(kThreads), 0, st, p); break;
+    case 256: hipLaunchKernelGGL((softmax_block_wide_kernel<256, VEC>), grid, dim3(kThreads), 0, st, p); break;
+    case 512: hipLaunchKernelGGL((softmax_block_wide_kernel<512, VEC>), grid, dim3(kThreads), 0, st, p); break;
+    case 1024: hipLaunchKernelGGL((softmax_block_wide_kernel<1024, VEC>), grid, dim3(kThreads), 0, st, p); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// Whether the wide form is the faster one, from 64 to 40000 rows of 256 to
+// 12000 columns (both forms in microseconds, block 128).  It spends a whole
+// chunk of 4096 columns on a shorter row, so with many short rows the forms
+// that pack rows into a wave win.  Aligned rows: 2000 x 1000 9.6 against 11.4,
+// 4000 x 1000 15.6 against 12.2; from 3000 columns on always (40000 x 3000 131
+// against 148).  Unaligned rows store byte by byte either way, and there the
+// wide form only pays where the others leave the chip idle (300 x 2001 8.3
+// against 14.1; 2000 x 2001 17.7 against 15.6).  Blocks of 512 and 1024 make
+// the walk of the other form shorter: the line lies at fewer rows.
+bool wide_is_faster(const SoftmaxBlockParams& p, bool aligned)
+{
+    if (p.cols < 1 || (p.cols + p.block - 1) / p.block > kWideMaxBlk) return false;
+    const bool big = p.block > 256;
+    if (aligned) return p.cols >= 3000 || p.rows <= (big ? p.cols : 2 * p.cols);
+    return p.rows <= 1024 && p.cols >= (big ? 1500 : 512) && p.cols >= (big ? 8 : 4) * p.rows;
+}
+
 template <int NT, int KCH>
 hipError_t launch_block4(const SoftmaxBlockParams& p, hipStream_t st)
 {
@@ -297,20 +512,14 @@ hipError_t launch_block4(const SoftmaxBlockParams& p, hipStream_t st)
 
 hipError_t launch_softmax_block(const SoftmaxBlockParams& p, hipStream_t st)
 {
-    const bool vec = ((uintptr_t)p.s % 16 == 0) && (p.ld % 4 == 0) && (p.cols % 4 == 0) &&
-                     ((uintptr_t)p.codes % 4 == 0) && p.block <= 256;
-    if (vec) {
+    const bool aligned = ((uintptr_t)p.s % 16 == 0) && (p.ld % 4 == 0) && (p.cols % 4 == 0) &&
+                         ((uintptr_t)p.codes % 4 == 0);
+    int ncu = 0;
+    const hipError_t e = cu_count(&ncu);
+    if (e != hipSuccess) return e;
+    if (wide_is_faster(p, aligned)) return aligned ? launch_wide<true>(p, ncu, st) : launch_wide<false>(p, ncu, st);
+    if (aligned && p.block <= 256) {
         // one 1024-thread workgroup per CU when the rows fill every CU
-        static std::atomic<int> ncu_of[64] = {};    // CU count per device, read once
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        int ncu = (dev >= 0 && dev < 64) ? ncu_of[dev].load(std::memory_order_relaxed) : 0;
-        if (ncu == 0) {
-            e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-            if (e != hipSuccess) return e;
-            if (dev >= 0 && dev < 64) ncu_of[dev].store(ncu, std::memory_order_relaxed);
-        }
         const long long wg1024 = (p.rows + 4 * 16 - 1) / (4 * 16);
         if (wg1024 >= ncu) return p.cols >= 4096 ? launch_block4<1024, 512>(p, st) : launch_block4<1024, 256>(p, st);
         // fewer rows than CUs x 64: at most two 256-thread workgroups per CU

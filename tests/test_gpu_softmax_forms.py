@@ -1,0 +1,55 @@
+"""The forms of the softmax-block kernel (GPU): the wide one (a workgroup per
+row, chunks of 4096 columns) at the edges of its chunks and blocks, aligned
+and not, and the row-group and row-per-wave forms that the rule still picks.
+Codes, shifts, maxima and flags are bit-exact against the oracle, d within
+fp32 summation order (1e-5)."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2602_02071_amd.workloads import random_scores
+from test_gpu_softmax_block import _compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("block", [64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("cols", [4, 60, 1024, 4092, 4096, 4100, 8192, 8196, 12292])
+def test_wide_aligned(cols, block):
+    print(f"wide {cols} block {block}", flush=True)
+    _compare(random_scores(9, cols, seed=cols + block, std=5.0, masked_frac=0.02), block, ld=cols + 8)
+
+
+@pytest.mark.parametrize("block", [64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("cols", [513, 1999, 4095, 4097, 8191, 12289])
+def test_wide_unaligned(cols, block):
+    _compare(random_scores(7, cols, seed=cols + block, std=5.0, masked_frac=0.02), block)
+
+
+@pytest.mark.parametrize("lam,n_b0", [(0, 0), (2, 3), (-3, 1), (50, 2), (1, 200)])
+def test_wide_knobs_on_climbing_rows(lam, n_b0):
+    """Rows whose maximum moves at nearly every block (by small steps, about
+    one, and many at once), where the wide form's guess is often off; masked
+    rows and a masked start among them."""
+    rows, cols = 12, 9000
+    s = random_scores(rows, cols, seed=lam + 7, std=0.3)
+    s += (np.linspace(0, 1, cols, dtype=np.float32)[None, :] *
+          np.array([0, 1, 3, 8, 20, 60, 120, 250, 600, -50, -300, 5], np.float32)[:, None])
+    s[3, :5000] = -np.inf
+    s[11] = -np.inf
+    for block in (64, 256):
+        _compare(s, block, lam, n_b0)
+        _compare(s[:, :8999], block, lam, n_b0)
+
+
+@pytest.mark.parametrize("rows,cols,block", [
+    (1500, 4096, 128),       # wide: several rows per workgroup
+    (3000, 300, 64),         # row groups, 256 threads, wide steps
+    (9000, 200, 128),        # row groups, 256 threads
+    (16500, 132, 256),       # row groups, 1024 threads
+    (1030, 700, 512),        # a row per wave, aligned rows and a wide block
+    (1100, 515, 128),        # a row per wave, unaligned
+    (3, 70000, 64),          # more blocks than the wide form holds: row groups on long rows
+])
+def test_every_form(rows, cols, block):
+    _compare(random_scores(rows, cols, seed=rows, std=4.0, masked_frac=0.01), block)
