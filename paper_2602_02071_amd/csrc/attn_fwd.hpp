@@ -1004,6 +1004,26 @@ hipError_t launch_one(const AttnParams& p, hipStream_t st)
     return hipGetLastError();
 }
 
+// 128 rows on four waves against 256 on eight, where two such workgroups share
+// a CU: the same waves at work, half the step when items run out, and two
+// barriers of four waves instead of one of eight.  n8, n4: their items.
+// Measured in 12 classes of 32 shapes (times of 256 over 128 rows).  D * BLK =
+// 8192: causal at D = 128 0.97 to 1.34, mean 1.11 (the longest item ends
+// earlier); not causal 0.90 to 1.59, so only where the last round thins out:
+// fewer rounds (480 items for 288: 1.38 and 1.59), or at most half a second
+// round of 256-row items on rows long enough that an item's start does not
+// weigh (384 items of 1369 keys 1.06 and 1.14; of 300 keys 0.94).  FP8 Q/K
+// under a causal mask at D = 64: 0.98 to 1.23, mean 1.10.  Past four rounds
+// the two are alike.
+inline bool four_waves_are_faster(const AttnParams& p, int D, int block, int ncu, long long n8, long long n4)
+{
+    if (n8 > 4LL * ncu) return false;
+    if (p.causal && (p.qk_f8 ? (D == 64 || block == 64) : (D == 128 && block == 64))) return true;
+    if (D * block != 8192) return false;
+    return (n8 + ncu - 1) / ncu > (n4 + 2 * ncu - 1) / (2 * ncu) ||
+           (n8 > ncu && 2 * n8 <= 3LL * ncu && p.Sk >= 8 * block);
+}
+
 // The rows of a work item, by how many items that leaves for the CUs.  A wave
 // is bound by the latency of its own chain (QK^T, row maximum, decision, table
 // reads, PV), so a key block takes 3.0 us with eight waves on 256 rows, 2.2 us
@@ -1031,6 +1051,9 @@ hipError_t launch_rows(const AttnParams& p, hipStream_t st)
         if constexpr (kPerCu64 == 1)
             if ((flat + 127) / 128 * heads <= ncu)
                 return launch_one<D, BLK, 8, 2, CT, MODE, false, F8, TIE, DUMP>(p, st);
+        if constexpr (CT && MODE == kModeE2E && !TIE && kPerCu64 > 1)
+            if (four_waves_are_faster(p, D, BLK, ncu, (flat + 255) / 256 * heads, (flat + 127) / 128 * heads))
+                return launch_one<D, BLK, 4, 1, CT, MODE, false, F8, TIE, DUMP>(p, st);
     }
     return launch_one<D, BLK, 8, 1, CT, MODE, false, F8, TIE, DUMP>(p, st);
 }
