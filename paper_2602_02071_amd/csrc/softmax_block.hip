@@ -3,12 +3,12 @@
 // the restart decision of the B1 loop, the integer running maximum (Sec. 3.3),
 // T = HiF8(S - ref), P = HiF8(2^T), and the running denominator.
 //
-// One wave owns one row.  The row streams through registers 1024 columns at
-// a time (16 per lane, lane-interleaved so every load and store of the wave
-// is contiguous); blocks inside a chunk are processed in order, which is the
-// only sequential dependency of the method (the reference of block j depends
-// on the running maximum after block j-1).  HBM-bound: 4 B read and 1 B
-// written per score.
+// HBM-bound where rows fill the GPU: 4 B read and 1 B written per score.  The
+// only sequential dependency is that the reference of block j depends on the
+// running maximum after block j-1.  Three forms (launch_softmax_block picks):
+// a wave per row that walks 1024 columns at a time (16 per lane,
+// lane-interleaved so every load and store of the wave is contiguous; any
+// alignment), four rows per wave, and a workgroup per row.
 #include "common.hpp"
 
 namespace baps {
@@ -170,7 +170,8 @@ constexpr int kRowsPerWave4 = 4;
 // the kernel at 64 VGPRs (8 waves per SIMD), which suits grids of many
 // workgroups per CU and short rows; wider steps put more bytes in flight per
 // wave where fewer waves share a CU: 512 columns (96 VGPRs) for rows of at
-// least 4096 columns at 1024 threads, 1024 columns (162 VGPRs) for grids of
+// least 4096 columns at 1024 threads (here only with more blocks than the
+// wide form holds), 1024 columns (162 VGPRs) for grids of
 // at most two 256-thread workgroups per CU.
 template <int BLOCK, int NT, int KCH>
 __global__ __launch_bounds__(NT) void softmax_block4_kernel(SoftmaxBlockParams p)
