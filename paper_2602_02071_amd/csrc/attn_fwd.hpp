@@ -623,11 +623,20 @@ __global__ __launch_bounds__(64 * NW, 2) void baps_attn_fwd_kernel(AttnParams p)
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 } else {
+                    // (written with one base address per d chunk: one per read takes
+                    // the tile-level restart kernels at D = 64, block 64 from 125 to
+                    // 130 VGPRs, past the 128 that let two workgroups share a CU)
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int i = 0; i < kN; ++i)
-                        sacc[i % kKT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(k_frag(i)), as_bf16x8(qop[i / kKT]),
-                                                                              sacc[i % kKT], 0, 0, 0);
+                    for (int kk = 0; kk < kDK; ++kk) {
+                        const char* kp = kt_lds + koff[kk];
+#pragma unroll
+                        for (int kt = 0; kt < kKT; ++kt) {
+                            const u32x4 a = *reinterpret_cast<const u32x4*>(kp + kt * 32 * C::kRowBytes);
+                            sacc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(qop[kk]), sacc[kt],
+                                                                               0, 0, 0);
+                        }
+                    }
                     __builtin_amdgcn_sched_group_barrier(0x100, kKReads, 0);          // LDS reads
 #pragma unroll
                     for (int i = 0; i < kN - kKReads; ++i) {
