@@ -40,6 +40,7 @@
 //     t+1 runs on the VALU while the PV MFMAs of tile t execute.
 #pragma once
 #include "common.hpp"
+#include "prefill_form.hpp"
 
 namespace baps {
 
@@ -1013,38 +1014,8 @@ hipError_t launch_one(const AttnParams& p, hipStream_t st)
     return hipGetLastError();
 }
 
-// 128 rows on four waves against 256 on eight, where two such workgroups share
-// a CU: the same waves at work, half the step when items run out, and two
-// barriers of four waves instead of one of eight.  n8, n4: their items.
-// Measured in 12 classes of 32 shapes (times of 256 over 128 rows).  D * BLK =
-// 8192: causal at D = 128 0.97 to 1.34, mean 1.11 (the longest item ends
-// earlier); not causal 0.90 to 1.59, so only where the last round thins out:
-// fewer rounds (480 items for 288: 1.38 and 1.59), or at most half a second
-// round of 256-row items on rows long enough that an item's start does not
-// weigh (384 items of 1369 keys 1.06 and 1.14; of 300 keys 0.94).  FP8 Q/K
-// under a causal mask at D = 64: 0.98 to 1.23, mean 1.10.  Past four rounds
-// the two are alike.
-inline bool four_waves_are_faster(const AttnParams& p, int D, int block, int ncu, long long n8, long long n4)
-{
-    if (n8 > 4LL * ncu) return false;
-    if (p.causal && (p.qk_f8 ? (D == 64 || block == 64) : (D == 128 && block == 64))) return true;
-    if (D * block != 8192) return false;
-    return (n8 + ncu - 1) / ncu > (n4 + 2 * ncu - 1) / (2 * ncu) ||
-           (n8 > ncu && 2 * n8 <= 3LL * ncu && p.Sk >= 8 * block);
-}
-
-// The rows of a work item, by how many items that leaves for the CUs.  A wave
-// is bound by the latency of its own chain (QK^T, row maximum, decision, table
-// reads, PV), so a key block takes 3.0 us with eight waves on 256 rows, 2.2 us
-// with eight on 128 rows (each block's keys split over two waves of the same
-// rows) and 1.8 us with four on 64 rows (likewise) at D = 128, block 128: the
-// smallest tile wins while all its items run at once, the largest once the
-// items queue.  64 rows: up to three workgroups per CU at D * BLK = 4096, two
-// at 8192 and one at 16384, where the K/V buffers fill the LDS; 128 rows: one.
-// Measured over 340 shapes (1 to 16 sequences of 100 to 4096 queries, contexts
-// to 9000 keys): 1.27x 256 rows alone in the geometric mean, at most 6 %
-// slower anywhere (GQA 32/8, D = 128: 512 queries 19.3 -> 11.5 us, 512 queries
-// on 4096 keys 101.5 -> 56.8 us, 1024 queries 33.2 -> 25.8 us).
+// The form of a call without tile-level restart (the forms that
+// prefill_form never picks are not built)
 template <int D, int BLK, bool CT, int MODE, bool F8, bool TIE, bool DUMP>
 hipError_t launch_rows(const AttnParams& p, hipStream_t st)
 {
@@ -1052,17 +1023,13 @@ hipError_t launch_rows(const AttnParams& p, hipStream_t st)
         int ncu = 0;
         const hipError_t e = cu_count(&ncu);
         if (e != hipSuccess) return e;
-        const long long flat = (long long)p.Sq * (p.Hq / p.Hkv), heads = (long long)p.Hkv * p.B;
-        constexpr int kPerCu64 = D * BLK <= 4096 ? 3 : (D * BLK <= 8192 ? 2 : 1);
-        if ((flat + 63) / 64 * heads <= (long long)kPerCu64 * ncu)
-            return launch_one<D, BLK, 4, 2, CT, MODE, false, F8, TIE, DUMP>(p, st);
-        // (with two or three 64-row workgroups per CU the 128-row items never fit when the 64-row ones do not)
-        if constexpr (kPerCu64 == 1)
-            if ((flat + 127) / 128 * heads <= ncu)
-                return launch_one<D, BLK, 8, 2, CT, MODE, false, F8, TIE, DUMP>(p, st);
-        if constexpr (CT && MODE == kModeE2E && !TIE && kPerCu64 > 1)
-            if (four_waves_are_faster(p, D, BLK, ncu, (flat + 255) / 256 * heads, (flat + 127) / 128 * heads))
-                return launch_one<D, BLK, 4, 1, CT, MODE, false, F8, TIE, DUMP>(p, st);
+        const PrefillForm f = prefill_form(PrefillShape{D, BLK, p.Sq, p.Sk, p.Hq / p.Hkv, (long long)p.Hkv * p.B,
+                                                        p.causal != 0, F8, MODE == kModeE2E, !CT, TIE, ncu});
+        if (f.nw == 4 && f.kw == 2) return launch_one<D, BLK, 4, 2, CT, MODE, false, F8, TIE, DUMP>(p, st);
+        if constexpr (D * BLK == 16384)
+            if (f.kw == 2) return launch_one<D, BLK, 8, 2, CT, MODE, false, F8, TIE, DUMP>(p, st);
+        if constexpr (CT && MODE == kModeE2E && !TIE && (D * BLK == 8192 || (F8 && D * BLK < 8192)))
+            if (f.nw == 4) return launch_one<D, BLK, 4, 1, CT, MODE, false, F8, TIE, DUMP>(p, st);
     }
     return launch_one<D, BLK, 8, 1, CT, MODE, false, F8, TIE, DUMP>(p, st);
 }

@@ -1,24 +1,20 @@
-"""The rows per work item of the prefill kernel (GPU).
+"""The forms of the prefill kernel (GPU): 64, 128 or 256 query rows per work
+item on four or eight waves.
 
-The library gives a work item 64, 128 or 256 query rows by how many items
-that leaves; with 64 and 128 rows the waves split each key block's keys and
-exchange the row maxima.  Every row count is run with every softmax setup and
-Q/K format, on ragged tiles (150 query positions: the last tile holds 22 rows
-of 64 or 128) and on shapes right at the two limits of the rule."""
+With 64 rows, and with 128 on eight waves, the waves split each key block's
+keys and exchange the row maxima.  Every form of every head dimension and key
+block is run with every softmax setup and Q/K format, causal and not, on
+ragged tiles, and the kernel that each call launched is checked, so that a
+rule that moves a shape elsewhere cannot leave a form without its test."""
 import numpy as np
 import pytest
 
 import oracle as O
 from helpers import ARB_TOL, check_parity, dev_bf16, dev_u8, gpu_dump, lse_arb_tol
+from helpers_form import SETUPS, SIZES, form_of, forms, launched, launched_form, shape_for
 from paper_2602_02071_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
-
-CUS = 256
-# (D, block, rows per item) -> heads of 150 positions that land there (3 items of 64 rows, 2 of 128, 1 of 256)
-HEADS = {(128, 128, 64): 5, (128, 128, 128): 100, (128, 128, 256): 130, (128, 64, 64): 6, (128, 64, 256): 172,
-         (64, 64, 64): 7, (64, 64, 256): 260, (64, 128, 64): 5, (64, 128, 256): 172}
-SETUPS = ("e2e", "default", "exp2", "even", "fp8", "lambda9")
 
 
 def on_own_scores(q, k, v, shape, block, rows, o, lse, fp8, **okw):
@@ -37,7 +33,7 @@ def on_own_scores(q, k, v, shape, block, rows, o, lse, fp8, **okw):
     assert np.all(np.abs(lse - res[1]) <= lse_arb_tol(res[1], np.isfinite(acc).sum(axis=1)))
 
 
-def run(shape, block, label, setup="e2e", heads=None, step=7, own_scores=False):
+def run(shape, block, label, setup="e2e", heads=None, step=7, own_scores=False, form=None):
     import torch
     import paper_2602_02071_amd as baps
     B, Hq, Hkv, Sq, Sk, D, causal = shape
@@ -62,8 +58,11 @@ def run(shape, block, label, setup="e2e", heads=None, step=7, own_scores=False):
     o = torch.full((B, Hq, Sq, D), float("nan"), dtype=torch.float32, device="cuda:0")
     lse = torch.full((B, Hq, Sq), float("nan"), dtype=torch.float32, device="cuda:0")
     print(f"{label}: {shape} block {block}", flush=True)
-    baps.baps_attention_fwd_ex(qt, kt, dev_bf16(v), o, lse, B, Hq, Hkv, Sq, Sk, D, causal, block, **kn)
-    torch.cuda.synchronize()
+    vt = dev_bf16(v)
+    _, names = launched(lambda: baps.baps_attention_fwd_ex(qt, kt, vt, o, lse, B, Hq, Hkv, Sq, Sk, D, causal, block,
+                                                           **kn))
+    want = form_of(shape, block, setup) if form is None else form
+    assert launched_form(names) == (D, block) + want, (names, want)
     assert not torch.isnan(o).any() and not torch.isnan(lse).any(), "rows never written"
     heads = sorted({0, Hq // 2, Hq - 1}) if heads is None else heads
     pos = np.array(sorted(set(range(0, Sq, step)) | {min(63, Sq - 1), min(64, Sq - 1), min(127, Sq - 1), Sq - 1}))
@@ -76,20 +75,21 @@ def run(shape, block, label, setup="e2e", heads=None, step=7, own_scores=False):
         check_parity(q, k, v, shape, block, o, lse, rows=rows, label=label, fp8=fp8, **okw)
 
 
-@pytest.mark.parametrize("setup", SETUPS)
-@pytest.mark.parametrize("key", sorted(HEADS), ids=lambda k: "d%d-b%d-rows%d" % k)
-def test_every_row_count(key, setup):
-    D, block, rows = key
-    h = HEADS[key]
-    per_cu = {4096: 3, 8192: 2, 16384: 1}[D * block]
-    want = 64 if 3 * h <= per_cu * CUS else (128 if per_cu == 1 and 2 * h <= CUS else 256)
-    assert want == rows                                      # the shape lands where it is meant to
-    run((1, h, h, 150, 333, D, setup != "exp2"), block, f"rows {rows} {setup}", setup)
+EVERY = [(size, setup, causal, form) for size in SIZES for setup in SETUPS for causal in (True, False)
+         for form in forms(size, setup, causal)]
 
 
-@pytest.mark.parametrize("Sq,rows", [(2048, 64), (2049, 128), (4096, 128), (4097, 256)])
-def test_limits_of_the_rule(Sq, rows):
-    run((1, 8, 8, Sq, 500, 128, False), 128, f"{rows} rows at {Sq} positions", step=97)
+@pytest.mark.parametrize("size,setup,causal,form", EVERY,
+                         ids=["d%d-b%d-%s-%s-%dx%d" % (s + (t, "causal" if c else "full") + f) for s, t, c, f in EVERY])
+def test_every_form(size, setup, causal, form):
+    shape = shape_for(size, setup, causal, form)
+    assert shape is not None, "no shape takes this form"
+    run(shape, size[1], f"form {form} {setup}", setup, step=max(7, shape[3] // 40), own_scores=setup == "fp8", form=form)
+
+
+@pytest.mark.parametrize("Sq,form", [(2048, (4, 2)), (2049, (8, 2)), (4096, (8, 2)), (4097, (8, 1))])
+def test_limits_of_the_rule(Sq, form):
+    run((1, 8, 8, Sq, 500, 128, False), 128, f"{form} at {Sq} positions", step=97, form=form)
 
 
 def test_queries_before_the_first_key():
@@ -108,10 +108,10 @@ def test_queries_before_the_first_key():
 
 FOUR_WAVES = [
     # D, block, FP8, causal, positions, heads, keys: 128-row items on four waves
-    (128, 64, False, True, 150, 180, 333),
-    (128, 64, True, True, 150, 180, 333),
+    (128, 64, False, True, 150, 180, 300),
+    (128, 64, True, True, 150, 180, 300),
     (64, 64, True, True, 150, 260, 333),
-    (64, 128, True, True, 150, 172, 333),
+    (64, 128, True, True, 150, 172, 300),
     (64, 128, False, False, 100, 260, 333),      # one round of 128-row items, two of 256-row ones
     (128, 64, False, False, 100, 260, 333),
     (64, 128, False, False, 150, 300, 1100),     # half a second round of 256-row items
@@ -122,7 +122,4 @@ FOUR_WAVES = [
 @pytest.mark.parametrize("key", FOUR_WAVES, ids=lambda k: "-".join(map(str, k)))
 def test_four_waves(key):
     D, block, fp8, causal, sq, h, sk = key
-    n4, n8 = -(-sq // 128) * h, -(-sq // 256) * h
-    assert -(-sq // 64) * h > {4096: 3, 8192: 2}[D * block] * CUS and n8 <= 4 * CUS      # not the 64-row items
-    assert causal or -(-n8 // CUS) > -(-n4 // (2 * CUS)) or (CUS < n8 <= 1.5 * CUS and sk >= 8 * block)
-    run((1, h, h, sq, sk, D, causal), block, f"four waves {key}", "fp8" if fp8 else "e2e", own_scores=fp8)
+    run((1, h, h, sq, sk, D, causal), block, f"four waves {key}", "fp8" if fp8 else "e2e", own_scores=fp8, form=(4, 1))
