@@ -46,25 +46,53 @@ inline bool four_waves_are_faster(const PrefillShape& s, long long n256, long lo
 // with eight on 128 rows (each block's keys split over two waves of the same
 // rows) and 1.8 us with four on 64 rows (likewise) at D = 128, block 128: the
 // smallest tile wins while all its items run at once, the largest once the
-// items queue.  64 rows: up to three workgroups per CU at D * block = 4096, two
-// at 8192 and one at 16384, where the K/V buffers fill the LDS; 128 rows: one.
-// Measured over 340 shapes (1 to 16 sequences of 100 to 4096 queries, contexts
-// to 9000 keys): 1.27x 256 rows alone in the geometric mean, at most 6 %
-// slower anywhere (GQA 32/8, D = 128: 512 queries 19.3 -> 11.5 us, 512 queries
-// on 4096 keys 101.5 -> 56.8 us, 1024 queries 33.2 -> 25.8 us).
+// items queue (GQA 32/8, D = 128: 512 queries 19.3 -> 11.5 us, 512 queries on
+// 4096 keys 101.5 -> 56.8 us, 1024 queries 33.2 -> 25.8 us).  Below, D * block
+// names the K/V buffers' size: 4096, 8192 or 16384.  Factors are times of 256
+// rows over the form's.
 inline PrefillForm prefill_form(const PrefillShape& s)
 {
     const PrefillForm rows256{8, 1}, rows128{8, 2}, rows64{4, 2}, four_waves{4, 1};
     if (s.block < 64) return rows256;
     const int size = s.D * s.block;
-    const long long ncu = s.ncu, flat = s.Sq * s.group;
+    const long long ncu = s.ncu, flat = s.Sq * s.group, Sk = s.Sk;
+    const long long q = s.Sq < Sk ? s.Sq : Sk;              // query positions that see a key, causal
     const long long n64 = (flat + 63) / 64 * s.heads, n128 = (flat + 127) / 128 * s.heads,
                     n256 = (flat + 255) / 256 * s.heads;
-    const int per_cu = size <= 4096 ? 3 : (size <= 8192 ? 2 : 1);
-    if (n64 <= per_cu * ncu) return rows64;
-    // (with two or three 64-row workgroups per CU the 128-row items never fit when the 64-row ones do not)
-    if (per_cu == 1 && n128 <= ncu) return rows128;
-    if (s.alg1 && !s.full_table && !s.ties_even && per_cu > 1 && four_waves_are_faster(s, n256, n128))
+    // 64-row workgroups whose LDS fits a CU: K/V buffers, the table (8 KiB, or 16
+    // for ties to even and the full one; none in eq. (2)'s fp32 setup, which fits
+    // as often) and the exchanged row maxima
+    const int lds64 = 8 * size + (s.ties_even || s.full_table ? 16 : 8) * 1024 + 1024 + 256;
+    const int fit64 = 160 * 1024 / lds64;
+    if (!s.full_table) {
+        if (n64 <= ncu) return rows64;
+        // A second one per CU, if its LDS fits there (ties to even at 8192: 81
+        // KiB, not); if not, where causal items end at very different times
+        // (700 positions of 24 heads 1.4; not causal 0.6 to 0.9).
+        const bool uneven = s.causal && (3 * q >= 2 * Sk ? Sk >= 500 || (Sk >= 300 && 2 * n64 <= 3 * ncu)
+                                                         : 5 * q >= 2 * Sk && Sk >= 1500);
+        if (size < 16384 && n64 <= 2 * ncu && (fit64 >= 2 || uneven)) return rows64;
+        if (fit64 >= 3 && n64 <= 3 * ncu) return rows64;
+        // (at 8192 and below 128-row items never all fit when 64-row ones do not)
+        if (size == 16384 && n128 <= ncu) return rows128;
+    } else {
+        // The full table costs a workgroup 2 us before its first block: more,
+        // smaller workgroups only where rows are long or many and a head's K/V
+        // stay on one XCD, are few, or are long enough to hide that (one per
+        // CU: 256 positions of 48 heads 1.3 at 16384, 300 of 51 heads 0.86; two
+        // at 8192, where they do not fit at once: 500 positions of 37 heads
+        // 0.58, 3000 causal positions of 8 heads 1.5).
+        const bool local = s.heads % 8 == 0 || s.heads <= 32;      // K/V stay on one XCD, or are few
+        const bool ramp = s.causal && 3 * q >= 2 * Sk;
+        if (n64 <= ncu && (flat > 128 ? Sk >= 1024 || flat > 512 || (local && (size > 4096 || Sk >= 256)) : Sk >= 4096))
+            return rows64;
+        if (size == 4096 && n64 <= 2 * ncu && ((flat > 256 && Sk >= 1024) || (flat > 512 && local))) return rows64;
+        if (size == 4096 && n64 <= 3 * ncu && ((ramp && Sk >= 1500) || (s.causal && 3 * q >= Sk && Sk >= 700 && local)))
+            return rows64;
+        if (size == 8192 && n64 <= 2 * ncu && ramp && (Sk >= 2048 || (Sk >= 600 && 2 * n64 <= 3 * ncu))) return rows64;
+        if (size == 16384 && n128 <= ncu && flat > 128) return rows128;
+    }
+    if (s.alg1 && !s.full_table && !s.ties_even && size < 16384 && four_waves_are_faster(s, n256, n128))
         return four_waves;
     return rows256;
 }

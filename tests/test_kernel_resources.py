@@ -35,3 +35,12 @@ def test_two_prefill_workgroups_per_cu():
             assert 2 * (res["lds"] + 4 * block * 2 * D) <= 160 << 10, (key, res)
     assert seen >= 10
 
+
+
+def test_rows64_workgroups_fit_as_the_rule_counts():
+    """prefill_form's LDS per 64-row workgroup is at least the kernel's, and says right how many (of up to three) fit."""
+    for (D, block, nw, kw, ct, mode, tile, f8, persist, even, dump), res in _prefill().items():
+        if (nw, kw) == (4, 2) and not dump:
+            lds = res["lds"] + 4 * block * 2 * D
+            counted = 8 * D * block + (16 if even or not ct else 8) * 1024 + 1024 + 256
+            assert lds <= counted and min(3, (160 << 10) // lds) == min(3, (160 << 10) // counted), (D, block, ct, mode, even, lds)

@@ -1,0 +1,31 @@
+"""The rule that picks the prefill kernel's form (CPU only): shapes on both
+sides of its lines, each with the form that measured faster there."""
+import pytest
+
+from helpers_code_object import READELF, kernel_resources
+from helpers_form import SETUPS, SIZES, form_of, forms
+
+ROWS64, ROWS128, ROWS256, FOUR = (4, 2), (8, 2), (8, 1), (4, 1)
+
+
+def _form(heads, Sq, Sk, D, block, causal, setup="e2e", group=1):
+    return form_of((1, heads * group, heads, Sq, Sk, D, causal), block, setup)
+
+
+# ties to even and lambda > 8 hold 16 KiB of table: two 64-row workgroups do not share a CU at D * block = 8192
+@pytest.mark.parametrize("heads,Sq,Sk,D,block,causal,setup,want", [
+    (80, 256, 256, 64, 128, False, "even", ROWS256),
+    (200, 70, 70, 128, 64, True, "even", ROWS256),
+    (24, 700, 700, 128, 64, True, "even", ROWS64),
+    (64, 256, 256, 64, 128, False, "even", ROWS64),
+    (150, 70, 70, 64, 128, False, "lambda9", ROWS256),
+    (37, 500, 500, 64, 128, False, "lambda9", ROWS256),
+    (128, 256, 256, 128, 64, False, "lambda9", ROWS256),
+    (8, 3000, 3000, 64, 128, True, "lambda9", ROWS64),
+    (170, 230, 230, 64, 64, False, "lambda9", ROWS256),
+    (100, 70, 70, 128, 128, True, "lambda9", ROWS256),
+    (16, 1024, 1024, 64, 64, False, "lambda9", ROWS64),
+    (80, 256, 256, 64, 128, False, "e2e", ROWS64),
+])
+def test_larger_tables(heads, Sq, Sk, D, block, causal, setup, want):
+    assert _form(heads, Sq, Sk, D, block, causal, setup) == want
