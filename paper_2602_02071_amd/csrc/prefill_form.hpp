@@ -64,7 +64,15 @@ inline PrefillForm prefill_form(const PrefillShape& s)
     // as often) and the exchanged row maxima
     const int lds64 = 8 * size + (s.ties_even || s.full_table ? 16 : 8) * 1024 + 1024 + 256;
     const int fit64 = 160 * 1024 / lds64;
-    if (!s.full_table) {
+    // One 256-row item holds a head's rows and more than half of the CUs have
+    // one: smaller items read K/V again (256 heads, 128 rows, 5000 keys, D = 64,
+    // block 128: 0.79; 200 heads, 500 keys 0.92 at 16384).  Short causal rows at
+    // D = 64 still gain (133 heads of 150 positions 1.22), and so do ties to
+    // even at 16384, whose lookups weigh more than the reads (200 heads, 128
+    // rows, 1500 keys 1.2).
+    const bool held = flat <= 256 && 2 * s.heads > ncu && n256 <= ncu && !(s.ties_even && size == 16384) &&
+                      !(s.causal && s.D == 64 && flat > 128 && Sk <= 2 * flat);
+    if (!s.full_table && !held) {
         if (n64 <= ncu) return rows64;
         // A second one per CU, if its LDS fits there (ties to even at 8192: 81
         // KiB, not); if not, where causal items end at very different times
@@ -75,7 +83,8 @@ inline PrefillForm prefill_form(const PrefillShape& s)
         if (fit64 >= 3 && n64 <= 3 * ncu) return rows64;
         // (at 8192 and below 128-row items never all fit when 64-row ones do not)
         if (size == 16384 && n128 <= ncu) return rows128;
-    } else {
+    }
+    if (s.full_table && !held) {
         // The full table costs a workgroup 2 us before its first block: more,
         // smaller workgroups only where rows are long or many and a head's K/V
         // stay on one XCD, are few, or are long enough to hide that (one per
@@ -92,6 +101,8 @@ inline PrefillForm prefill_form(const PrefillShape& s)
         if (size == 8192 && n64 <= 2 * ncu && ramp && (Sk >= 2048 || (Sk >= 600 && 2 * n64 <= 3 * ncu))) return rows64;
         if (size == 16384 && n128 <= ncu && flat > 128) return rows128;
     }
+    // (four waves: two items of a head's 129 to 256 rows, short causal ones only)
+    if (held && !(s.causal && flat > 128 && Sk <= 2 * flat)) return rows256;
     if (s.alg1 && !s.full_table && !s.ties_even && size < 16384 && four_waves_are_faster(s, n256, n128))
         return four_waves;
     return rows256;

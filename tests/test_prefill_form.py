@@ -29,3 +29,20 @@ def _form(heads, Sq, Sk, D, block, causal, setup="e2e", group=1):
 ])
 def test_larger_tables(heads, Sq, Sk, D, block, causal, setup, want):
     assert _form(heads, Sq, Sk, D, block, causal, setup) == want
+
+
+# one 256-row item per head on more than half of the CUs reads K/V once
+@pytest.mark.parametrize("heads,Sq,Sk,D,block,causal,setup,want", [
+    (256, 128, 5000, 64, 128, False, "e2e", ROWS256),
+    (256, 70, 1500, 128, 64, True, "fp8", ROWS256),
+    (200, 128, 500, 128, 128, True, "e2e", ROWS256),
+    (200, 100, 100, 64, 64, False, "default", ROWS256),
+    (170, 150, 150, 128, 64, False, "exp2", ROWS256),
+    (256, 128, 300, 64, 128, True, "fp8", ROWS256),
+    (133, 150, 150, 64, 128, True, "e2e", ROWS64),
+    (128, 197, 197, 64, 128, False, "e2e", ROWS64),
+    (200, 128, 1500, 128, 128, False, "even", ROWS128),
+    (200, 197, 197, 64, 128, True, "fp8", FOUR),
+])
+def test_one_item_per_head(heads, Sq, Sk, D, block, causal, setup, want):
+    assert _form(heads, Sq, Sk, D, block, causal, setup) == want
