@@ -80,7 +80,17 @@ inline PrefillForm prefill_form(const PrefillShape& s)
         const bool uneven = s.causal && (3 * q >= 2 * Sk ? Sk >= 500 || (Sk >= 300 && 2 * n64 <= 3 * ncu)
                                                          : 5 * q >= 2 * Sk && Sk >= 1500);
         if (size < 16384 && n64 <= 2 * ncu && (fit64 >= 2 || uneven)) return rows64;
-        if (fit64 >= 3 && n64 <= 3 * ncu) return rows64;
+        // A third: causal (1.05 to 1.4; 150 positions 0.97 unless the 256-row
+        // items do not fit at once, 1.12), 256-row items that do not (144 heads
+        // of 257 positions 1.14), or long rows (4096 positions of 12 heads 1.04)
+        // whose K/V stay on one XCD, are few or have as many queries to share
+        // them (65 heads, 512 on 6000 keys: 0.87).  Other short ones lose: 197
+        // positions of 192 heads 0.94, 256 of 170 0.81.
+        const bool local = s.heads % 8 == 0 || s.heads <= 32 || 2 * s.Sq >= Sk;
+        if (fit64 >= 3 && n64 <= 3 * ncu &&
+            ((s.causal && 3 * q >= Sk && (flat > 192 || n256 > ncu)) ||
+             (flat > 256 && (n256 > ncu || (Sk >= 1024 && local)))))
+            return rows64;
         // (at 8192 and below 128-row items never all fit when 64-row ones do not)
         if (size == 16384 && n128 <= ncu) return rows128;
     }

@@ -46,3 +46,22 @@ def test_larger_tables(heads, Sq, Sk, D, block, causal, setup, want):
 ])
 def test_one_item_per_head(heads, Sq, Sk, D, block, causal, setup, want):
     assert _form(heads, Sq, Sk, D, block, causal, setup) == want
+
+
+# a third 64-row workgroup per CU at D = 64, block 64
+@pytest.mark.parametrize("heads,Sq,Sk,causal,setup,want", [
+    (192, 197, 197, False, "e2e", ROWS256),
+    (170, 256, 256, False, "default", ROWS256),
+    (85, 500, 500, False, "e2e", ROWS256),
+    (109, 400, 400, False, "exp2", ROWS256),
+    (65, 512, 6000, True, "e2e", ROWS256),
+    (260, 128, 4000, True, "e2e", ROWS256),
+    (256, 150, 150, True, "e2e", ROWS256),
+    (192, 197, 197, True, "e2e", ROWS64),
+    (144, 257, 257, False, "e2e", ROWS64),
+    (12, 4096, 4096, False, "e2e", ROWS64),
+    (8, 6000, 7500, True, "e2e", ROWS64),
+    (340, 70, 70, True, "default", ROWS64),
+])
+def test_third_workgroup(heads, Sq, Sk, causal, setup, want):
+    assert _form(heads, Sq, Sk, 64, 64, causal, setup) == want
