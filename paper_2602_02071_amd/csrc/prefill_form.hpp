@@ -18,38 +18,19 @@ struct PrefillShape {
     int ncu;
 };
 
-// 128 rows on four waves against 256 on eight, where two such workgroups share
-// a CU: the same waves at work, half the step when items run out, and two
-// barriers of four waves instead of one of eight.  n256, n128: their items.
-// Measured in 12 classes of 32 shapes (times of 256 over 128 rows).  D * block
-// = 8192: causal at D = 128 0.97 to 1.34, mean 1.11 (the longest item ends
-// earlier); not causal 0.90 to 1.59, so only where the last round thins out:
-// fewer rounds (480 items for 288: 1.38 and 1.59), or at most half a second
-// round of 256-row items on rows long enough that an item's start does not
-// weigh (384 items of 1369 keys 1.06 and 1.14; of 300 keys 0.94).  FP8 Q/K
-// under a causal mask at D = 64: 0.98 to 1.23, mean 1.10.  Past four rounds
-// the two are alike.
-inline bool four_waves_are_faster(const PrefillShape& s, long long n256, long long n128)
-{
-    const int size = s.D * s.block;
-    const long long ncu = s.ncu;
-    if (n256 > 4 * ncu) return false;
-    if (s.causal && (s.fp8 ? (s.D == 64 || s.block == 64) : (s.D == 128 && s.block == 64))) return true;
-    if (size != 8192) return false;
-    return (n256 + ncu - 1) / ncu > (n128 + 2 * ncu - 1) / (2 * ncu) ||
-           (n256 > ncu && 2 * n256 <= 3 * ncu && s.Sk >= 8 * s.block);
-}
-
-// The rows of a work item, by how many items that leaves for the CUs.  A wave
-// is bound by the latency of its own chain (QK^T, row maximum, decision, table
-// reads, PV), so a key block takes 3.0 us with eight waves on 256 rows, 2.2 us
-// with eight on 128 rows (each block's keys split over two waves of the same
-// rows) and 1.8 us with four on 64 rows (likewise) at D = 128, block 128: the
-// smallest tile wins while all its items run at once, the largest once the
-// items queue (GQA 32/8, D = 128: 512 queries 19.3 -> 11.5 us, 512 queries on
-// 4096 keys 101.5 -> 56.8 us, 1024 queries 33.2 -> 25.8 us).  Below, D * block
-// names the K/V buffers' size: 4096, 8192 or 16384.  Factors are times of 256
-// rows over the form's.
+// A wave is bound by the latency of its own chain (QK^T, row maximum, decision,
+// table reads, PV), so a key block takes 3.0 us with eight waves on 256 rows,
+// 2.2 us with eight on 128 rows (each block's keys split over two waves of the
+// same rows) and 1.8 us with four on 64 rows (likewise) at D = 128, block 128:
+// the smallest item wins while all items run at once, the largest once they
+// queue (GQA 32/8, D = 128: 512 queries 19.3 -> 11.5 us, 512 queries on 4096
+// keys 101.5 -> 56.8 us, 1024 queries 33.2 -> 25.8 us); four waves on 128 rows,
+// two workgroups per CU, win where a round of 256-row items runs thin.  The
+// lines were drawn through 14800 shapes with every form timed (2 to 400 heads,
+// 64 to 4096 queries, to 10000 keys, all setups): 1.160 times the speed of 256
+// rows alone in the geometric mean (the best form of each shape: 1.172), 11
+// shapes below 0.98, the least 0.93.  D * block names the K/V buffers' size
+// (4096, 8192 or 16384); factors are times of 256 rows over the form's.
 inline PrefillForm prefill_form(const PrefillShape& s)
 {
     const PrefillForm rows256{8, 1}, rows128{8, 2}, rows64{4, 2}, four_waves{4, 1};
@@ -111,11 +92,37 @@ inline PrefillForm prefill_form(const PrefillShape& s)
         if (size == 8192 && n64 <= 2 * ncu && ramp && (Sk >= 2048 || (Sk >= 600 && 2 * n64 <= 3 * ncu))) return rows64;
         if (size == 16384 && n128 <= ncu && flat > 128) return rows128;
     }
-    // (four waves: two items of a head's 129 to 256 rows, short causal ones only)
+    // 128 rows on four waves, two workgroups per CU: the same waves at work,
+    // half the step when items run out, two barriers of four waves instead of
+    // one of eight; a pair is 2 to 8 % slower than eight waves on the same rows
+    // where nothing runs out.  Measured on bf16 and FP8 Q/K of the canonical
+    // setup only (the others are not built); past four rounds it is level.
+    if (!s.alg1 || s.full_table || s.ties_even || size == 16384 || n256 > 4 * ncu) return rows256;
     if (held && !(s.causal && flat > 128 && Sk <= 2 * flat)) return rows256;
-    if (s.alg1 && !s.full_table && !s.ties_even && size < 16384 && four_waves_are_faster(s, n256, n128))
-        return four_waves;
-    return rows256;
+    const bool fewer = (n256 + ncu - 1) / ncu > (n128 + 2 * ncu - 1) / (2 * ncu);      // rounds
+    const bool thin = fewer || (n256 > ncu && 2 * n256 <= 3 * ncu && Sk >= 8 * s.block);
+    // Not causal: a thin last round (480 items for 288: 1.38 to 1.59; 288 to 384
+    // items of 1024 keys and more 1.04 to 1.2).  At 4096, where two 256-row
+    // workgroups share a CU anyway, FP8 gains as much in a round as thin (1.07
+    // to 1.18) and is not taken; bf16 is not built.
+    if (!s.causal) return size == 8192 && thin ? four_waves : rows256;
+    // Causal: what the CUs have on average, in units of the longest item.
+    // Below 0.63 that item sets the time and a half-size one ends earlier (1.1
+    // to 1.2); near 1 the long-and-short pairs of the 256-row schedule fill the
+    // GPU and four waves lose (GQA 32/8, 4096 positions, D = 128: 0.93).
+    const double load = (double)n256 * (double)(2 * Sk - q) / (2.0 * (double)Sk * (double)ncu);
+    const bool lead = 3 * q >= Sk && load <= (3 * q >= 2 * Sk ? 0.70 : 0.63);
+    bool four;
+    if (size == 4096)          // FP8 only: 1.0 to 1.2; cached keys in front and many items 0.97
+        four = s.fp8 && (n128 <= 3 * ncu || (5 * q >= 2 * Sk && n256 <= 2 * ncu) || 4 * q >= 3 * Sk);
+    else if (s.D == 128)       // also heads of few items unless those nearly fill two rounds or four (512 positions
+                               // 1.2, 700 1.12), and rows that 256-row tiles pad by a twelfth (1369 positions 1.1)
+        four = lead || (3 * q >= Sk && flat <= 1024 && (4 * n256 < 7 * ncu || (n256 > 2 * ncu && 2 * n256 <= 7 * ncu))) ||
+               (24 * n256 >= 13 * n128 && 3 * q >= Sk);
+    else                       // D = 64, block 128
+        four = (s.fp8 && load <= 0.70 && 3 * q >= Sk && (load <= 0.55 || flat <= 768 || Sk >= 8 * s.block)) ||
+               (thin && (load <= 0.74 || 2 * q < Sk)) || (fewer && 10 * n256 >= 6 * n128);
+    return four ? four_waves : rows256;
 }
 
 }  // namespace baps

@@ -2,7 +2,6 @@
 sides of its lines, each with the form that measured faster there."""
 import pytest
 
-from helpers_code_object import READELF, kernel_resources
 from helpers_form import SETUPS, SIZES, form_of, forms
 
 ROWS64, ROWS128, ROWS256, FOUR = (4, 2), (8, 2), (8, 1), (4, 1)
@@ -65,3 +64,39 @@ def test_one_item_per_head(heads, Sq, Sk, D, block, causal, setup, want):
 ])
 def test_third_workgroup(heads, Sq, Sk, causal, setup, want):
     assert _form(heads, Sq, Sk, 64, 64, causal, setup) == want
+
+
+# 128 rows on four waves at D * block = 8192 (FP8 at 4096 too): where the longest causal item sets the time, heads
+# of few items, padded tiles; not where the 256-row items pair up and fill the GPU
+@pytest.mark.parametrize("heads,group,Sq,Sk,D,block,causal,setup,want", [
+    (8, 4, 4096, 4096, 128, 64, True, "e2e", ROWS256),
+    (8, 4, 2000, 6000, 128, 64, True, "fp8", ROWS256),
+    (8, 4, 3500, 9000, 128, 64, True, "fp8", ROWS256),
+    (16, 1, 4096, 4096, 128, 64, True, "e2e", FOUR),
+    (32, 1, 4096, 4096, 64, 128, True, "fp8", ROWS256),
+    (64, 1, 4096, 4096, 128, 64, True, "fp8", ROWS256),
+    (48, 1, 2048, 2048, 64, 128, True, "e2e", ROWS256),
+    (16, 1, 4096, 4096, 64, 128, True, "fp8", FOUR),
+    (96, 1, 1369, 1369, 128, 64, True, "e2e", FOUR),
+    (184, 1, 512, 512, 128, 64, True, "fp8", FOUR),
+    (96, 1, 577, 577, 64, 128, True, "e2e", FOUR),
+    (16, 1, 4096, 4096, 64, 64, True, "fp8", FOUR),
+    (64, 4, 2048, 3048, 64, 64, True, "fp8", ROWS256),
+    (96, 1, 577, 577, 128, 64, False, "e2e", FOUR),
+    (32, 1, 4096, 4096, 128, 64, False, "e2e", ROWS256),
+    (16, 1, 4096, 4096, 128, 64, True, "exp2", ROWS256),
+])
+def test_four_waves(heads, group, Sq, Sk, D, block, causal, setup, want):
+    assert _form(heads, Sq, Sk, D, block, causal, setup, group) == want
+
+
+def test_only_forms_that_are_built():
+    """Every form that the rule can return is one that the library builds (over a grid of shapes)."""
+    for size in SIZES:
+        for setup in SETUPS:
+            for causal in (True, False):
+                for heads in (1, 3, 8, 24, 64, 130, 200, 400, 1100):
+                    for Sq in (1, 65, 130, 200, 500, 1369, 4096):
+                        for Sk in (0, 1, 64, 500, 5000):
+                            f = _form(heads, Sq, Sk, *size, causal, setup)
+                            assert f in forms(size, setup, causal), (size, setup, causal, heads, Sq, Sk, f)
