@@ -47,12 +47,12 @@ inline PrefillForm prefill_form(const PrefillShape& s)
     const int fit64 = 160 * 1024 / lds64;
     // One 256-row item holds a head's rows and more than half of the CUs have
     // one: smaller items read K/V again (256 heads, 128 rows, 5000 keys, D = 64,
-    // block 128: 0.79; 200 heads, 500 keys 0.92 at 16384).  Short causal rows at
-    // D = 64 still gain (133 heads of 150 positions 1.22), and so do ties to
-    // even at 16384, whose lookups weigh more than the reads (200 heads, 128
+    // block 128: 0.79; 200 heads, 500 keys 0.92 at 16384).  Short rows at D = 64
+    // still gain (133 heads of 150 positions 1.12, causal 1.22), and so do ties
+    // to even at 16384, whose lookups weigh more than the reads (200 heads, 128
     // rows, 1500 keys 1.2).
     const bool held = flat <= 256 && 2 * s.heads > ncu && n256 <= ncu && !(s.ties_even && size == 16384) &&
-                      !(s.causal && s.D == 64 && flat > 128 && Sk <= 2 * flat);
+                      !(s.D == 64 && flat > 128 && Sk <= 2 * flat);
     if (!s.full_table && !held) {
         if (n64 <= ncu) return rows64;
         // A second one per CU, if its LDS fits there (ties to even at 8192: 81

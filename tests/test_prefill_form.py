@@ -39,6 +39,7 @@ def test_larger_tables(heads, Sq, Sk, D, block, causal, setup, want):
     (170, 150, 150, 128, 64, False, "exp2", ROWS256),
     (256, 128, 300, 64, 128, True, "fp8", ROWS256),
     (133, 150, 150, 64, 128, True, "e2e", ROWS64),
+    (170, 150, 150, 64, 128, False, "fp8", ROWS64),
     (128, 197, 197, 64, 128, False, "e2e", ROWS64),
     (200, 128, 1500, 128, 128, False, "even", ROWS128),
     (200, 197, 197, 64, 128, True, "fp8", FOUR),
