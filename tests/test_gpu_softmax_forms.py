@@ -53,3 +53,43 @@ def test_wide_knobs_on_climbing_rows(lam, n_b0):
 ])
 def test_every_form(rows, cols, block):
     _compare(random_scores(rows, cols, seed=rows, std=4.0, masked_frac=0.01), block)
+
+
+def test_wide_rows_that_climb_take_no_settling_one_by_one():
+    """Scores that climb by 6 log2 units per block at lambda 8, where the 8-bit cast rounds every few blocks'
+    T down to an integer: at most 1.6 times the time of level scores (settled block by block it was 2.6 times)."""
+    import torch
+    import paper_2602_02071_amd as baps
+    rows, cols, block, lam = 16384, 8192, 64, 8
+    level = torch.randn((rows, cols), device="cuda:0") * 0.05
+    climb = level + 6.2 * (torch.arange(cols, device="cuda:0") // block)
+    nblk = cols // block
+    codes = torch.empty((rows, cols), dtype=torch.uint8, device="cuda:0")
+    shift = torch.empty((rows, nblk), dtype=torch.int32, device="cuda:0")
+    m, d = torch.empty(rows, device="cuda:0"), torch.empty(rows, device="cuda:0")
+
+    def fastest(s):
+        best = float("inf")
+        for _ in range(12):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            baps.baps_softmax_block(s, rows, cols, cols, block, lam, 1, 0, codes, shift, m, d)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        return best
+
+    t_level, t_climb = fastest(level), fastest(climb)
+    print(f"level {t_level * 1e3:.0f} us, climbing {t_climb * 1e3:.0f} us", flush=True)
+    assert t_climb <= 1.6 * t_level
+
+
+@pytest.mark.parametrize("lam,step", [(1, 1.03), (1, 1.6), (2, 2.1), (4, 3.1), (8, 6.2), (50, 41.0)])
+def test_wide_rows_that_climb(lam, step):
+    """Several blocks of a chunk whose T the 8-bit cast rounds down to an integer, more chunks than one and a last
+    one that is short; at lambda 50 the cast rounds by up to 4."""
+    s = random_scores(6, 9000, seed=lam, std=0.05)
+    s += np.float32(step) * (np.arange(9000) // 64).astype(np.float32)
+    for block in (64, 128):
+        _compare(s, block, lam)
+        _compare(s[:, :8999], block, lam)
