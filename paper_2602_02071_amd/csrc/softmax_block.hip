@@ -170,8 +170,8 @@ constexpr int kRowsPerWave4 = 4;
 // the kernel at 64 VGPRs (8 waves per SIMD), which suits grids of many
 // workgroups per CU and short rows; wider steps put more bytes in flight per
 // wave where fewer waves share a CU: 512 columns (96 VGPRs) for rows of at
-// least 4096 columns at 1024 threads (here only with more blocks than the
-// wide form holds), 1024 columns (162 VGPRs) for grids of
+// least 4096 columns at 1024 threads (rows just behind a chunk of the wide
+// form, and more blocks than it holds), 1024 columns (162 VGPRs) for grids of
 // at most two 256-thread workgroups per CU.
 template <int BLOCK, int NT, int KCH>
 __global__ __launch_bounds__(NT) void softmax_block4_kernel(SoftmaxBlockParams p)
@@ -481,21 +481,29 @@ hipError_t launch_wide(const SoftmaxBlockParams& p, int ncu, hipStream_t st)
     return hipGetLastError();
 }
 
-// Whether the wide form is the faster one, from 64 to 40000 rows of 256 to
-// 12000 columns (both forms in microseconds, block 128).  It spends a whole
-// chunk of 4096 columns on a shorter row, so with many short rows the forms
-// that pack rows into a wave win.  Aligned rows: 2000 x 1000 9.6 against 11.4,
-// 4000 x 1000 15.6 against 12.2; from 3000 columns on always (40000 x 3000 131
-// against 148).  Unaligned rows store byte by byte either way, and there the
-// wide form only pays where the others leave the chip idle (300 x 2001 8.3
-// against 14.1; 2000 x 2001 17.7 against 15.6).  Blocks of 512 and 1024 make
-// the walk of the other form shorter: the line lies at fewer rows.
+// Whether the wide form is the faster one, drawn through 2290 aligned shapes of
+// 4 to 65536 rows and 4 to 50000 columns (the other form in front, us): 1.90
+// times as fast in the geometric mean, no shape below 0.98.  It spends a whole
+// chunk of 4096 columns on a shorter rest of a row, so with many short rows the
+// forms that pack rows into a wave win (4000 x 1000, block 128: 12.2 against
+// 15.6; 2000 x 1000 11.4 against 9.6), and so they do with many rows that end
+// just behind a chunk (16384 x 4100, block 256: 72 against 92, block 64: 82
+// against 92; 4096 x 4100, block 1024: 23 against 27; but 8192 x 4100, block 64,
+// 117 against 50: the wide steps of 256 threads spill there).  Blocks of 512 and 1024 make the walk of
+// the other form shorter: their lines lie at fewer rows; block 256 is between
+// (4096 x 2048 15.5 against 16.2, 16384 x 3000 55 against 57).  Unaligned rows
+// store byte by byte either way, and there the wide form only pays where the
+// others leave the chip idle (300 x 2001 8.3 against 14.1; 2000 x 2001 17.7
+// against 15.6).
 bool wide_is_faster(const SoftmaxBlockParams& p, bool aligned)
 {
     if (p.cols < 1 || (p.cols + p.block - 1) / p.block > kWideMaxBlk) return false;
     const bool big = p.block > 256;
-    if (aligned) return p.cols >= 3000 || p.rows <= (big ? p.cols : 2 * p.cols);
-    return p.rows <= 1024 && p.cols >= (big ? 1500 : 512) && p.cols >= (big ? 8 : 4) * p.rows;
+    if (!aligned) return p.rows <= 1024 && p.cols >= (big ? 1500 : 512) && p.cols >= (big ? 8 : 4) * p.rows;
+    if (p.cols > 4096 && p.cols < 5200) return p.rows <= (big ? 2048 : (p.block == 256 ? 7000 : 10000));
+    if (p.cols >= 3000) return p.block != 256 || p.cols >= 3300 || p.rows <= 10000;
+    if (p.block == 256) return p.rows <= 2 * p.cols && (p.rows <= 2048 || 5 * p.rows <= 9 * p.cols);
+    return p.rows <= (big ? 1 : 2) * p.cols;
 }
 
 template <int NT, int KCH>

@@ -8,6 +8,7 @@ import pytest
 
 import oracle as O
 from paper_2602_02071_amd.workloads import random_scores
+from helpers_form import launched
 from test_gpu_softmax_block import _compare
 
 pytestmark = pytest.mark.gpu
@@ -42,17 +43,39 @@ def test_wide_knobs_on_climbing_rows(lam, n_b0):
         _compare(s[:, :8999], block, lam, n_b0)
 
 
-@pytest.mark.parametrize("rows,cols,block", [
-    (1500, 4096, 128),       # wide: several rows per workgroup
-    (3000, 300, 64),         # row groups, 256 threads, wide steps
-    (9000, 200, 128),        # row groups, 256 threads
-    (16500, 132, 256),       # row groups, 1024 threads
-    (1030, 700, 512),        # a row per wave, aligned rows and a wide block
-    (1100, 515, 128),        # a row per wave, unaligned
-    (3, 70000, 64),          # more blocks than the wide form holds: row groups on long rows
+@pytest.mark.parametrize("rows,cols,block,kernel", [
+    (1500, 4096, 128, "block_wide_kernel<128, true>"),           # several rows per workgroup
+    (3000, 300, 64, "block4_kernel<64, 256, 1024>"),       # row groups, 256 threads, wide steps
+    (9000, 200, 128, "block4_kernel<128, 256, 256>"),      # row groups, 256 threads
+    (16500, 132, 256, "block4_kernel<256, 1024, 256>"),    # row groups, 1024 threads
+    (16500, 4100, 256, "block4_kernel<256, 1024, 512>"),   # the same, rows just behind a chunk of the wide form
+    (1030, 700, 512, "block_kernel<512>"),                 # a row per wave, aligned rows and a wide block
+    (1100, 515, 128, "block_kernel<128>"),                 # a row per wave, unaligned
+    (3, 70000, 64, "block4_kernel<64, 256, 1024>"),        # more blocks than the wide form holds
 ])
-def test_every_form(rows, cols, block):
-    _compare(random_scores(rows, cols, seed=rows, std=4.0, masked_frac=0.01), block)
+def test_every_form(rows, cols, block, kernel):
+    s = random_scores(rows, cols, seed=rows, std=4.0, masked_frac=0.01)
+    _, names = launched(lambda: _compare(s, block))
+    assert len(names) == 1 and "softmax_" + kernel in names[0], names
+
+
+@pytest.mark.parametrize("rows,cols,block,wide", [
+    (16384, 4100, 64, False), (16384, 4100, 256, False), (32768, 4500, 128, False), (4096, 4100, 1024, False),
+    (3000, 4100, 512, False), (8192, 4100, 256, False), (4096, 2048, 256, False), (16384, 3000, 256, False),
+    (8192, 4100, 64, True), (16384, 8196, 128, True), (16384, 4096, 256, True), (16384, 5200, 64, True),
+    (2048, 4100, 1024, True), (2048, 1024, 256, True), (16384, 3000, 128, True),
+])
+def test_lines_of_the_wide_form(rows, cols, block, wide):
+    """Rows that end just behind a chunk, and the other lines of the rule, by the kernel that runs."""
+    import torch
+    import paper_2602_02071_amd as baps
+    nblk = -(-cols // block)
+    s = torch.zeros((rows, cols), device="cuda:0")
+    codes = torch.empty((rows, cols), dtype=torch.uint8, device="cuda:0")
+    shift = torch.empty((rows, nblk), dtype=torch.int32, device="cuda:0")
+    m, d = torch.empty(rows, device="cuda:0"), torch.empty(rows, device="cuda:0")
+    _, names = launched(lambda: baps.baps_softmax_block(s, rows, cols, cols, block, 1, 1, 0, codes, shift, m, d))
+    assert len(names) == 1 and ("wide" in names[0]) == wide, names
 
 
 def test_wide_rows_that_climb_take_no_settling_one_by_one():
