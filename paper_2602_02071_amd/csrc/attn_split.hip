@@ -38,23 +38,23 @@ __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast
 constexpr int kRows = 16;            // query rows per workgroup (16x16x32 MFMA columns)
 constexpr int kSlotKeys = 32;        // keys per wave and block, and per ring slot
 
-// A workgroup's waves are KW key slots (wave % KW takes 32 keys of a block)
+// A workgroup's W waves are KW key slots (wave % KW takes 32 keys of a block)
 // times BG block groups (wave / KW takes every BG-th block of the split: the
-// blocks are independent once the references are known).  Two workgroups of
-// four waves share a CU, or, where the grid holds at most one per CU (BIG),
-// one of eight with twice the LDS: either way eight waves hide each other's
-// latency and 128 KiB of ring keep the memory busy.
-template <int D, int BLK, bool BIG>
+// blocks are independent once the references are known), with 16 KiB of ring
+// each.  launch_split_rt picks four waves, two workgroups of which share a CU,
+// or, where the grid holds at most one per CU, eight; or one group alone.
+template <int D, int BLK, int W>
 struct SCfg {
-    static constexpr int kWaves = BIG ? 8 : 4;
+    static constexpr int kWaves = W;
     static constexpr int kKeySlots = BLK / kSlotKeys;
     static constexpr int kGroups = kWaves / kKeySlots;
     static constexpr int kRowBytes = 2 * D;
     static constexpr int kCPR = D / 8;                          // 16-byte chunks per row
     static constexpr int kSlotBytes = kSlotKeys * kRowBytes;
     static constexpr int kIPS = kSlotBytes / 1024;              // wave-wide loads per slot
-    static constexpr int kRW = ((BIG ? 128 : 64) * 1024) / (kWaves * kSlotBytes);   // ring slots per wave
+    static constexpr int kRW = 16 * 1024 / kSlotBytes;          // ring slots per wave
     static constexpr int kLdsBytes = kWaves * kRW * kSlotBytes;
+    static_assert(kGroups >= 1 && kWaves == kGroups * kKeySlots, "whole block groups");
     static_assert(kRW >= 2 && kRW * kIPS <= 63, "ring slots");
 };
 
@@ -116,10 +116,10 @@ __device__ __forceinline__ RowInfo row_info(const AttnParams& p, int tile, int g
 // ---------------------------------------------------------------------------
 // 1. scores: acc and block maxima of one key split
 // ---------------------------------------------------------------------------
-template <int D, int BLK, bool F8, int RT, bool BIG>
-__global__ __launch_bounds__(BIG ? 512 : 256, 2) void split_scores_kernel(SplitParams sp)
+template <int D, int BLK, bool F8, int RT, int W>
+__global__ __launch_bounds__(64 * W, 2) void split_scores_kernel(SplitParams sp)
 {
-    using C = SCfg<D, BLK, BIG>;
+    using C = SCfg<D, BLK, W>;
     constexpr int NW = C::kWaves, KW = C::kKeySlots, BG = C::kGroups;
     constexpr int RW = C::kRW;
     constexpr int kDK = D / 32;
@@ -296,10 +296,10 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void split_scores_kernel(SplitP
 constexpr int kWinFloats = 256;      // block maxima per LDS window of the replay
 
 // RT tiles of 16 rows per workgroup share every V (and, in the scores pass, K) read.
-template <int D, int BLK, int RT, bool BIG>
-__global__ __launch_bounds__(BIG ? 512 : 256, 2) void split_pv_kernel(SplitParams sp)
+template <int D, int BLK, int RT, int W>
+__global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
 {
-    using C = SCfg<D, BLK, BIG>;
+    using C = SCfg<D, BLK, W>;
     constexpr int NW = C::kWaves, KW = C::kKeySlots, BG = C::kGroups;
     constexpr int RW = C::kRW;
     constexpr int kDT = D / 16;
@@ -764,18 +764,18 @@ __global__ __launch_bounds__(256) void split_combine_kernel(SplitParams sp)
             empty ? ninf : 0.69314718055994531f * (rr + (log2f(dx) + (float)kCodeBiasLog2));
 }
 
-template <int D, int BLK, int RT, bool BIG>
-hipError_t launch_split_big(const SplitParams& sp, hipStream_t st)
+template <int D, int BLK, int RT, int W>
+hipError_t launch_split_waves(const SplitParams& sp, hipStream_t st)
 {
-    using C = SCfg<D, BLK, BIG>;
+    using C = SCfg<D, BLK, W>;
     static DeviceOnce attr_set;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (!attr_set.is_done(dev)) {
-        const void* fns[] = {reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, false, RT, BIG>),
-                             reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, true, RT, BIG>),
-                             reinterpret_cast<const void*>(&split_pv_kernel<D, BLK, RT, BIG>)};
+        const void* fns[] = {reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, false, RT, W>),
+                             reinterpret_cast<const void*>(&split_scores_kernel<D, BLK, true, RT, W>),
+                             reinterpret_cast<const void*>(&split_pv_kernel<D, BLK, RT, W>)};
         for (const void* fn : fns) {
             e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes);
             if (e != hipSuccess) return e;
@@ -786,11 +786,11 @@ hipError_t launch_split_big(const SplitParams& sp, hipStream_t st)
     const long long flat = (long long)p.Sq * (p.Hq / p.Hkv);
     const unsigned tiles = (unsigned)((flat + RT * kRows - 1) / (RT * kRows));
     const dim3 grid(tiles * (unsigned)sp.nsplit, (unsigned)p.Hkv, (unsigned)p.B), block(64 * C::kWaves);
-    if (p.qk_f8) hipLaunchKernelGGL((split_scores_kernel<D, BLK, true, RT, BIG>), grid, block, C::kLdsBytes, st, sp);
-    else hipLaunchKernelGGL((split_scores_kernel<D, BLK, false, RT, BIG>), grid, block, C::kLdsBytes, st, sp);
+    if (p.qk_f8) hipLaunchKernelGGL((split_scores_kernel<D, BLK, true, RT, W>), grid, block, C::kLdsBytes, st, sp);
+    else hipLaunchKernelGGL((split_scores_kernel<D, BLK, false, RT, W>), grid, block, C::kLdsBytes, st, sp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((split_pv_kernel<D, BLK, RT, BIG>), grid, block, C::kLdsBytes, st, sp);
+    hipLaunchKernelGGL((split_pv_kernel<D, BLK, RT, W>), grid, block, C::kLdsBytes, st, sp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((split_combine_kernel<D>), dim3((unsigned)flat, (unsigned)p.Hkv, (unsigned)p.B), dim3(256), 0,
@@ -798,6 +798,14 @@ hipError_t launch_split_big(const SplitParams& sp, hipStream_t st)
     return hipGetLastError();
 }
 
+// The waves of a workgroup.  Where the grid holds at most one per CU, eight
+// share the replay of the rows and hide each other's latency (32 rows: 1.03 to
+// 1.2 times as fast as four over 1600 shapes).  16 rows on so few workgroups
+// means that a split is a single block; then only many rows on many blocks give
+// eight waves work (8 rows on 256 blocks: 19.6 us a call, with four waves 21.2;
+// otherwise four are 2 % faster), and of blocks of 32 or 64 keys one group is
+// enough for up to four rows (16 heads on 130 keys, block 32: 14.9 us with four
+// waves, 14.0 with one).
 template <int D, int BLK, int RT>
 hipError_t launch_split_rt(const SplitParams& sp, hipStream_t st)
 {
@@ -807,7 +815,11 @@ hipError_t launch_split_rt(const SplitParams& sp, hipStream_t st)
     const AttnParams& p = sp.a;
     const long long flat = (long long)p.Sq * (p.Hq / p.Hkv);
     const long long wgs = (flat + RT * kRows - 1) / (RT * kRows) * sp.nsplit * p.Hkv * p.B;
-    return wgs <= ncu ? launch_split_big<D, BLK, RT, true>(sp, st) : launch_split_big<D, BLK, RT, false>(sp, st);
+    if (wgs <= ncu && (RT == 2 || (flat > 4 && sp.nblk >= 128))) return launch_split_waves<D, BLK, RT, 8>(sp, st);
+    if constexpr (RT == 1 && BLK < 128) {
+        if (sp.bps == 1 && flat <= 4) return launch_split_waves<D, BLK, RT, BLK / kSlotKeys>(sp, st);
+    }
+    return launch_split_waves<D, BLK, RT, 4>(sp, st);
 }
 
 template <int D, int BLK>

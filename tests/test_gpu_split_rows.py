@@ -1,5 +1,5 @@
 """The split-key path's workgroup shapes (GPU): one or two 16-row tiles per
-workgroup, four or eight waves, block groups within a workgroup, one, two or
+workgroup, one, two, four or eight waves, block groups within a workgroup, one, two or
 four rows per wave in the replay, and runs of dot products that end early.
 Every T, P and reference equals the one-pass kernels': O and lse agree with
 them to fp32 summation order, the restart counters exactly."""
@@ -7,22 +7,31 @@ import numpy as np
 import pytest
 
 from helpers import check_parity, dev_bf16, dev_u8, lse_agree
+from helpers_form import launched
 from paper_2602_02071_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
-    # B, Hq, Hkv, Sq, Sk, D, causal, block
-    (1, 2, 2, 17, 3001, 64, True, 64),       # 17 rows: one in the second tile; eight waves
-    (4, 32, 8, 8, 700, 128, True, 32),       # 32 rows, three and four blocks per split, 8 block groups
-    (1, 6, 2, 11, 5000, 128, True, 128),     # 33 rows: a workgroup of 32 rows and one of a single row
-    (2, 8, 2, 16, 2500, 64, False, 128),     # 64 rows
-    (4, 64, 16, 8, 2560, 64, True, 32),      # 20 blocks per split: 16 rows per workgroup although it has 32
-    (4, 32, 8, 4, 8192, 128, True, 128),     # 16 rows, 512 workgroups of four waves
-    (2, 16, 4, 4, 20000, 64, True, 64),      # 16 rows on 313 blocks: several windows of 64
-    (1, 8, 8, 6, 9000, 128, True, 32),       # 6 rows: two per wave
-    (8, 8, 8, 1, 600, 128, False, 64),       # one row, splits of two and one blocks for two block groups
+    # B, Hq, Hkv, Sq, Sk, D, causal, block; 16-row tiles and waves of a workgroup
+    ((1, 2, 2, 17, 3001, 64, True, 64), (2, 8)),       # 17 rows: one in the second tile
+    ((4, 32, 8, 8, 700, 128, True, 32), (2, 8)),       # 32 rows, three and four blocks per split, 8 block groups
+    ((1, 6, 2, 11, 5000, 128, True, 128), (2, 8)),     # 33 rows: a workgroup of 32 rows and one of a single row
+    ((2, 8, 2, 16, 2500, 64, False, 64), (2, 8)),      # 64 rows
+    ((4, 64, 16, 8, 2560, 64, True, 32), (1, 4)),      # 20 blocks per split: 16 rows per workgroup although it has 32
+    ((4, 32, 8, 4, 8192, 128, True, 128), (1, 4)),     # 16 rows, 512 workgroups
+    ((2, 16, 4, 4, 20000, 64, True, 64), (1, 4)),      # 16 rows on 313 blocks: several windows of 64
+    ((1, 8, 8, 6, 9000, 128, True, 32), (1, 4)),       # 6 rows: two per wave
+    ((8, 8, 8, 1, 600, 128, False, 64), (1, 4)),       # one row, splits of two blocks
+    ((10, 32, 8, 8, 2000, 128, True, 64), (2, 4)),     # 32 rows, more workgroups than CUs
+    ((1, 16, 16, 1, 130, 128, True, 32), (1, 1)),      # one block per split, one row: a group of one wave
+    ((1, 8, 2, 1, 1000, 64, True, 32), (1, 1)),        # four rows on that wave
+    ((4, 8, 8, 2, 300, 64, True, 64), (1, 2)),         # two rows, a group of two waves
+    ((1, 6, 2, 1, 650, 128, False, 64), (1, 2)),       # three rows
+    ((1, 8, 1, 1, 5000, 64, True, 32), (1, 8)),        # eight rows, one block per split, 157 blocks to replay
+    ((1, 16, 16, 1, 600, 64, True, 128), (1, 4)),      # one block per split, whose group has four waves
 ]
+IDS = ["x".join(map(str, s)) for s, _ in SHAPES]
 
 
 def _inputs(shape, seed):
@@ -31,14 +40,19 @@ def _inputs(shape, seed):
     return q, k, v
 
 
-def _pair(qt, kt, vt, shape, block, **kn):
+def _pair(qt, kt, vt, shape, block, form=None, **kn):
     """(o, lse, counts) of the split path and of the one-pass kernels."""
     import torch
     import paper_2602_02071_amd as baps
     out = []
     for split in (True, False):
         cnt = torch.zeros((shape[0] * shape[1], 2), dtype=torch.int64, device="cuda:0")
-        o, lse = baps.attention(qt, kt, vt, shape[6], block, split=split, restart_counts=cnt, **kn)
+        if split and form:
+            (o, lse), names = launched(lambda: baps.attention(qt, kt, vt, shape[6], block, split=True,
+                                                              restart_counts=cnt, **kn))
+            assert sum("split_pv_kernel<%d, %d, %d, %d>" % ((shape[5], block) + form) in n for n in names) == 1, names
+        else:
+            o, lse = baps.attention(qt, kt, vt, shape[6], block, split=split, restart_counts=cnt, **kn)
         torch.cuda.synchronize()
         out.append((o.float().cpu().numpy().reshape(-1, shape[5]).astype(np.float64),
                     lse.cpu().numpy().reshape(-1).astype(np.float64), cnt.cpu().numpy()))
@@ -52,20 +66,20 @@ def _agree(pair, rel=2e-5):
     assert np.array_equal(cnt, cnt1)
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
-def test_split_rows(shape):
+@pytest.mark.parametrize("shape,form", SHAPES, ids=IDS)
+def test_split_rows(shape, form):
     import paper_2602_02071_amd as baps
     print(f"split rows {shape}", flush=True)
     assert baps.baps_attention_split_workspace(*shape[:6], shape[7]) > 0
     q, k, v = _inputs(shape, sum(shape))
-    pair = _pair(dev_bf16(q), dev_bf16(k), dev_bf16(v), shape, shape[7])
+    pair = _pair(dev_bf16(q), dev_bf16(k), dev_bf16(v), shape, shape[7], form)
     _agree(pair)
     rows = np.arange(0, shape[0] * shape[1] * shape[3], 5)
     check_parity(q, k, v, shape[:7], shape[7], pair[0][0][rows], pair[0][1][rows], rows=rows,
                  label=f"split rows {shape}", same_kernels=False)
 
 
-@pytest.mark.parametrize("shape", SHAPES[:4], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [s for s, _ in SHAPES[:4] + SHAPES[9:15]], ids=IDS[:4] + IDS[9:15])
 def test_split_rows_knobs(shape):
     """FP8 Q/K, a diagonal B0 block, other thresholds, and bf16 O (one bf16 rounding of nearly equal values)."""
     q, k, v = _inputs(shape, 7)
