@@ -55,7 +55,7 @@ struct SCfg {
     static constexpr int kRW = 16 * 1024 / kSlotBytes;          // ring slots per wave
     static constexpr int kLdsBytes = kWaves * kRW * kSlotBytes;
     static_assert(kGroups >= 1 && kWaves == kGroups * kKeySlots, "whole block groups");
-    static_assert(kRW >= 2 && kRW * kIPS <= 63, "ring slots");
+    static_assert(kRW >= 2 && kRW <= 4 && kRW * kIPS <= 63, "ring slots");
 };
 
 template <int D>
@@ -249,6 +249,9 @@ __global__ __launch_bounds__(64 * W, 2) void split_scores_kernel(SplitParams sp)
                 }
             }
         }
+        // one block group: its waves stay on one block, whose rows are neighbours
+        // in memory (D = 128, block 128, 268 MB of K and V: 0.5 us of 24)
+        if constexpr (BG == 1 && KW > 1 && D == 128) __builtin_amdgcn_s_barrier();
         if (issued < mine) { issue_slot(issued); ++issued; }
         // mask keys past kmax; register i of tile t2 holds key key0 + 16*t2 + 4*grp + i
         if (key0 + kSlotKeys - 1 > kmax_lo) {
@@ -378,6 +381,8 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
     const long long row0 = bg * flat + (long long)tile * kTR;    // the workgroup's first row
     const uint32_t my_ring_lds = ring_lds + (uint32_t)(wave * RW * C::kSlotBytes);
     const char* my_ring = ring + wave * RW * C::kSlotBytes;
+    const int nrg = min(kTR / 8, (nr + 7) / 8);              // groups of 8 rows with a row
+    uint64_t tags = 0;                            // ndma after each of the last four slots, the latest lowest
     auto issue_slot = [&](int q) {               // keys [32*kw, +32) of the blocks
         const int run = q / (kRun + 1), u = q % (kRun + 1);
         const uint32_t dst = my_ring_lds + (uint32_t)((q % RW) * C::kSlotBytes);
@@ -386,6 +391,7 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
 #pragma unroll
             for (int t = 0; t < C::kIPS; ++t) {
                 if (run * kRun + t / (kTR / 8) >= mine) break;   // (the last run may hold fewer blocks)
+                if (t % (kTR / 8) >= nrg) continue;
                 const int n = bg0 + BG * (run * kRun + t / (kTR / 8));
                 const int rr = (t % (kTR / 8)) * 8 + lane / 8;
                 const int ch = (lane % 8) ^ (rr & 7);
@@ -404,11 +410,9 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
             }
             ndma += C::kIPS;
         }
+        tags = tags << 16 | (uint16_t)ndma;
     };
     const int nseq = mine + (mine + kRun - 1) / kRun;
-    // loads issued after slot q: kIPS per slot, fewer in the last run's dot products
-    const int last_a = ((mine + kRun - 1) / kRun - 1) * (kRun + 1);
-    const int short_by = C::kIPS - (mine - (mine - 1) / kRun * kRun) * (kTR / 8);
     int issued = 0;
     for (; issued < min(nseq, RW); ++issued) issue_slot(issued);
 
@@ -521,7 +525,7 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
 
     int q = 0;                                    // ring slot to consume next
     auto wait_slot = [&]() {
-        wait_vm((issued - 1 - q) * C::kIPS - (q < last_a && last_a < issued ? short_by : 0));
+        wait_vm((uint16_t)(ndma - (int)(tags >> 16 * (issued - 1 - q))));
     };
     auto next_slot = [&]() {
         if (issued < nseq) { issue_slot(issued); ++issued; }
@@ -534,8 +538,24 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
         // V's way from memory
         float fac[kRun][RT];
         u32x4 pop[kRun][RT];
+        f32x4 sacc[kRun][RT][2];
         wait_slot();
         const char* aslot = my_ring + (q % RW) * C::kSlotBytes;
+#pragma unroll
+        for (int u = 0; u < kRun; ++u) {
+            if (n0 + u >= mine) break;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int t2 = 0; t2 < 2; ++t2) {
+                    const int row = rt * kRows + c16;
+                    sacc[u][rt][t2] = *reinterpret_cast<const f32x4*>(aslot + u * kAccBytes + row * 128 + 16 * ((4 * t2 + grp) ^ (row & 7)));
+                }
+        }
+        // the slot goes back as soon as it is read: V streams on behind the
+        // gathers (4 sequences on 16384 keys, block 128: 26.4 -> 25.2 us)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        next_slot();
 #pragma unroll
         for (int u = 0; u < kRun; ++u) {
             if (n0 + u >= mine) break;
@@ -547,17 +567,12 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
                 dl[rt] *= fac[u][rt];
                 if (rj != ninf) cur[rt] = rj;
                 const float nref = (cur[rt] == ninf) ? 0.0f : -cur[rt];
-                f32x4 sacc[2];
-#pragma unroll
-                for (int t2 = 0; t2 < 2; ++t2) {
-                    sacc[t2] = *reinterpret_cast<const f32x4*>(aslot + u * kAccBytes + row * 128 + 16 * ((4 * t2 + grp) ^ (row & 7)));
-                    if (!ok[rt]) sacc[t2] = f32x4{ninf, ninf, ninf, ninf};
-                }
+                if (!ok[rt]) sacc[u][rt][0] = sacc[u][rt][1] = f32x4{ninf, ninf, ninf, ninf};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int t2 = e >> 1;
-                    const float t0 = __builtin_fmaf(sacc[t2][2 * (e & 1)], c, nref);
-                    const float t1 = __builtin_fmaf(sacc[t2][2 * (e & 1) + 1], c, nref);
+                    const float t0 = __builtin_fmaf(sacc[u][rt][t2][2 * (e & 1)], c, nref);
+                    const float t1 = __builtin_fmaf(sacc[u][rt][t2][2 * (e & 1) + 1], c, nref);
                     const uint32_t i0 = min(max(hif8::f2u(t0) >> kTabShift, (uint32_t)kCodeLo), (uint32_t)kCodeHi);
                     const uint32_t i1 = min(max(hif8::f2u(t1) >> kTabShift, (uint32_t)kCodeLo), (uint32_t)kCodeHi);
                     const uint32_t w = ((uint32_t)ctab[i0 - kCodeLo] | ((uint32_t)ctab[i1 - kCodeLo] << 16)) << 4;
@@ -566,8 +581,6 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
                 }
             }
         }
-        asm volatile("" ::: "memory");            // (the slot is read before it is filled again)
-        next_slot();
 #pragma unroll
         for (int u = 0; u < kRun; ++u) {
             if (n0 + u >= mine) break;
