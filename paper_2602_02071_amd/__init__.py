@@ -114,11 +114,13 @@ def _stream(stream):
         # The current stream of the current device.  torch.cuda.current_stream()
         # builds a Stream object around the same handle: 2.9 us of a call that
         # took 12.5 us in all with it; the lookup of the handle (not part of
-        # torch's public interface) takes 0.2.
+        # torch's public interface) takes 0.3.
         import torch
-        raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
-        if raw is not None and device is not None and torch.cuda.is_initialized():
-            return raw(device())
+        try:
+            if torch.cuda.is_initialized():
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
