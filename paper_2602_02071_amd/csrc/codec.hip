@@ -138,10 +138,11 @@ __global__ __launch_bounds__(kThreads) void hif8_decode_scalar_kernel(const uint
         x[i] = hif8::decode(codes[i]);
 }
 
-int grid_for(long long work_items, int per_cu)
+// Workgroups for work_items threads, per_cu for each CU at most (grid-stride beyond)
+int grid_for(long long work_items, int per_cu, int ncu)
 {
     long long g = (work_items + kThreads - 1) / kThreads;
-    const long long cap = 256LL * per_cu;        // grid-stride beyond
+    const long long cap = (long long)ncu * per_cu;
     if (g > cap) g = cap;
     if (g < 1) g = 1;
     return (int)g;
@@ -151,26 +152,32 @@ int grid_for(long long work_items, int per_cu)
 
 hipError_t launch_hif8_encode(const float* x, uint8_t* codes, long long n, bool saturate, bool even, hipStream_t st)
 {
+    int ncu = 0;
+    const hipError_t e = cu_count(&ncu);
+    if (e != hipSuccess) return e;
     const bool aligned = ((uintptr_t)x % 16 == 0) && ((uintptr_t)codes % 4 == 0);
-    const dim3 grid(grid_for(n / (4 * kEncUnroll) + 1, kEncPerCu));
+    const dim3 grid(grid_for(n / (4 * kEncUnroll) + 1, kEncPerCu, ncu));
     if (aligned && even)
         hipLaunchKernelGGL(hif8_encode_kernel<true>, grid, dim3(kThreads), 0, st, x, codes, n, (int)saturate);
     else if (aligned)
         hipLaunchKernelGGL(hif8_encode_kernel<false>, grid, dim3(kThreads), 0, st, x, codes, n, (int)saturate);
     else
-        hipLaunchKernelGGL(hif8_encode_scalar_kernel, dim3(grid_for(n, 8)), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL(hif8_encode_scalar_kernel, dim3(grid_for(n, 8, ncu)), dim3(kThreads), 0, st,
                            x, codes, n, (int)saturate, (int)even);
     return hipGetLastError();
 }
 
 hipError_t launch_hif8_decode(const uint8_t* codes, float* x, long long n, hipStream_t st)
 {
+    int ncu = 0;
+    const hipError_t e = cu_count(&ncu);
+    if (e != hipSuccess) return e;
     const bool aligned = ((uintptr_t)x % 16 == 0) && ((uintptr_t)codes % 4 == 0);
     if (aligned)
-        hipLaunchKernelGGL(hif8_decode_kernel, dim3(grid_for(n / (4 * kDecUnroll) + 1, kDecPerCu)), dim3(kThreads), 0, st,
+        hipLaunchKernelGGL(hif8_decode_kernel, dim3(grid_for(n / (4 * kDecUnroll) + 1, kDecPerCu, ncu)), dim3(kThreads), 0, st,
                            codes, x, n);
     else
-        hipLaunchKernelGGL(hif8_decode_scalar_kernel, dim3(grid_for(n, 8)), dim3(kThreads), 0, st, codes, x, n);
+        hipLaunchKernelGGL(hif8_decode_scalar_kernel, dim3(grid_for(n, 8, ncu)), dim3(kThreads), 0, st, codes, x, n);
     return hipGetLastError();
 }
 
