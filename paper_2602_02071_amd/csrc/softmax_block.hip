@@ -289,11 +289,11 @@ __global__ __launch_bounds__(NT) void softmax_block4_kernel(SoftmaxBlockParams p
 // at the references found.  The rule itself is serial, but the integer maximum
 // is nearly always the running maximum of the blocks' own ceil(maximum): each
 // lane takes that as its guess (a prefix maximum), and the rule is repeated with
-// the results in place of the ceils until nothing changes.  Where the 8-bit cast
+// its results in place of the wrong guesses until nothing changes.  Where the 8-bit cast
 // rounds a block's T down to an integer the first guess is one too high from
 // there on; the repeats mend all such blocks of a chunk at once (settling them
 // one by one took 348 us on 16384 x 8192 scores that climb 6 per block at lambda
-// 8, against 140 for the row-group form).  A thread sums its P relative to the latest integer
+// 8, against 140 for the row-group form and 128 so).  A thread sums its P relative to the latest integer
 // maximum by exact powers of two.  VEC: 16-byte aligned rows of a multiple of
 // 4 columns (4 adjacent columns per lane); else columns go lane by lane.
 //
@@ -382,9 +382,9 @@ __global__ __launch_bounds__(kThreads) void softmax_block_wide_kernel(SoftmaxBlo
                 const bool in_row = jl < kNB && j < nblk;
                 const float h = in_row ? ceilf(M) : ninf;
                 // lanes 0 .. last hold the blocks.  hc: what m is taken to rise to
-                // at each, first the ceil of its own maximum, then what the rule
-                // made of it (the first k lanes are right after k repeats: at most
-                // last of them)
+                // at each, first the ceil of its own maximum, then, where that was
+                // wrong, what the rule made of it (the first k lanes are right
+                // after k repeats: at most last of them)
                 const int last = min(kNB - 64 * st, nblk - ch * kNB - 64 * st) - 1;
                 float hc = h, g, m_new;
                 bool restart;
@@ -394,8 +394,9 @@ __global__ __launch_bounds__(kThreads) void softmax_block_wide_kernel(SoftmaxBlo
                     if (M != ninf) tq = hif8::round(M - g);       // g = -inf gives +inf: restart
                     restart = j < p.n_b0 || ceilf(tq) > (float)p.lambda;
                     m_new = restart ? fmaxf(g, h) : g + fmaxf(0.0f, ceilf(tq));
-                    if (it >= last || !__any(lane <= last && m_new != fmaxf(g, hc))) break;
-                    hc = lane <= last && m_new > g ? m_new : ninf;
+                    const bool wrong = m_new != fmaxf(g, hc);     // (never behind the last block)
+                    if (it >= last || !__any(wrong)) break;
+                    if (wrong) hc = m_new > g ? m_new : ninf;
                 }
                 const float ref = lane > last ? ninf : (restart ? m_new : g);
                 const bool rst = restart;

@@ -107,7 +107,7 @@ def test_wide_rows_that_climb_take_no_settling_one_by_one():
     assert t_climb <= 1.6 * t_level
 
 
-@pytest.mark.parametrize("lam,step", [(1, 1.03), (1, 1.6), (2, 2.1), (4, 3.1), (8, 6.2), (50, 41.0)])
+@pytest.mark.parametrize("lam,step", [(1, 0.3), (8, 0.3), (1, 1.03), (1, 1.6), (2, 2.1), (4, 3.1), (8, 6.2), (50, 41.0)])
 def test_wide_rows_that_climb(lam, step):
     """Several blocks of a chunk whose T the 8-bit cast rounds down to an integer, more chunks than one and a last
     one that is short; at lambda 50 the cast rounds by up to 4."""
