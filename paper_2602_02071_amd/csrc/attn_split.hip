@@ -431,6 +431,7 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
     const int tagv = ndma;                        // ndma after the V ring's first loads
     auto wait_win = [&](int i) { wait_vm(ndma - (i < nearly ? tagc + i + 1 : tagv + (i - nearly) + 1)); };
     const float* win = &s_win[wave][0][0];
+    const float x_still = p.dec_x0 > 0.0f ? 0.0f : ninf;   // (lambda < 0 restarts below m as well)
     auto replay = [&](auto rows_per_wave) {
         constexpr int RPW = decltype(rows_per_wave)::value;
         constexpr int L = 64 / RPW, kWB = kWinFloats / RPW;
@@ -456,6 +457,16 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
                     const float ceil_ac = ceilf(amax * c);
                     const bool in_b0 = jb < p.n_b0 || (p.b0_last && jb == last_blk);
                     const bool in_split = row_ok && jb >= j0 && jb < j1;
+                    // no block above m (nearly every step of a long row): none
+                    // restarts or moves it, and m is the reference of them all
+                    // (131072 keys, block 128: 109.1 -> 106.0 us a call)
+                    if (!__any(vis && !(__builtin_fmaf(amax, c, -m) <= x_still))) {
+                        if (in_split) {
+                            refs_l[srow * kMaxBps + (jb - j0)] = vis ? m : ninf;
+                            n_visit += vis && !in_b0 ? 1u : 0u;
+                        }
+                        continue;
+                    }
                     const float h = vis ? ceil_ac : ninf;
                     int lo = 0;
                     for (;;) {

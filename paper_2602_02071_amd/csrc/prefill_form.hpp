@@ -19,9 +19,10 @@ struct PrefillShape {
 };
 
 // A wave is bound by the latency of its own chain (QK^T, row maximum, decision,
-// table reads, PV), so a key block takes 3.0 us with eight waves on 256 rows,
+// table reads, PV), so a key block takes 3.5 us with eight waves on 256 rows,
 // 2.2 us with eight on 128 rows (each block's keys split over two waves of the
-// same rows) and 1.8 us with four on 64 rows (likewise) at D = 128, block 128:
+// same rows) and 1.5 us with four on 64 rows (likewise) at D = 128, block 128
+// (bf16, one workgroup on every CU, 64 blocks against 32):
 // the smallest item wins while all items run at once, the largest once they
 // queue (GQA 32/8, D = 128: 512 queries 19.3 -> 11.5 us, 512 queries on 4096
 // keys 101.5 -> 56.8 us, 1024 queries 33.2 -> 25.8 us); four waves on 128 rows,

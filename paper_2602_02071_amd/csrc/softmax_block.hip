@@ -299,7 +299,7 @@ __global__ __launch_bounds__(NT) void softmax_block4_kernel(SoftmaxBlockParams p
 //
 // The other kernels give a row 16 or 64 lanes and walk it in steps: with few
 // rows that walk, not memory, is the time (300 rows of 30000 columns 158 us,
-// here 22; 4096 x 4096 41 -> 20 us; 16384 x 8192 142 -> 126 us, 5.5 TB/s).
+// here 22; 4096 x 4096 41 -> 20 us; 16384 x 8192, back to back, 126 -> 120 us, 5.6 TB/s).
 constexpr int kWideMaxBlk = 1024;                 // blocks per row (their references stay in LDS)
 
 template <int BLOCK, bool VEC>

@@ -90,6 +90,17 @@ def test_split_rows_knobs(shape):
     _agree(_pair(dev_bf16(q), dev_bf16(k), dev_bf16(v), shape, shape[7], out_bf16=True), rel=2.0 ** -8)
 
 
+@pytest.mark.parametrize("lam", [1, -2])
+def test_split_replay_below_the_maximum(lam):
+    """Steps of the replay whose blocks all lie below the maximum, with and without restarts there (lambda < 0),
+    behind a first block that holds it; some of those steps end just above it."""
+    shape = (1, 8, 2, 1, 40000, 64, False, 32)
+    q, k, v = _inputs(shape, 23)
+    k[:, :, :32] += np.uint16(2 << 7)             # bf16 bits: times 4
+    k[:, :, 30000] += np.uint16(3 << 7)           # times 8
+    _agree(_pair(dev_bf16(q), dev_bf16(k), dev_bf16(v), shape, shape[7], lam=lam))
+
+
 @pytest.mark.parametrize("delta", [0.02, 0.9, 3.0])
 def test_split_replay_of_a_climbing_maximum(delta):
     """Scores that climb by delta log2 units per block: small steps that the
