@@ -459,13 +459,16 @@ __global__ __launch_bounds__(64 * W, 2) void split_pv_kernel(SplitParams sp)
                     const bool in_split = row_ok && jb >= j0 && jb < j1;
                     // no block above m (nearly every step of a long row): none
                     // restarts or moves it, and m is the reference of them all
-                    // (131072 keys, block 128: 109.1 -> 106.0 us a call)
-                    if (!__any(vis && !(__builtin_fmaf(amax, c, -m) <= x_still))) {
-                        if (in_split) {
-                            refs_l[srow * kMaxBps + (jb - j0)] = vis ? m : ninf;
-                            n_visit += vis && !in_b0 ? 1u : 0u;
+                    // (131072 keys, block 128: 109.1 -> 106.4 us a call; 32
+                    // rows gain less, and 0.25 us of 28.3 is lost on 24 blocks)
+                    if constexpr (RT == 1) {
+                        if (!__any(vis && !(__builtin_fmaf(amax, c, -m) <= x_still))) {
+                            if (in_split) {
+                                refs_l[srow * kMaxBps + (jb - j0)] = vis ? m : ninf;
+                                n_visit += vis && !in_b0 ? 1u : 0u;
+                            }
+                            continue;
                         }
-                        continue;
                     }
                     const float h = vis ? ceil_ac : ninf;
                     int lo = 0;
