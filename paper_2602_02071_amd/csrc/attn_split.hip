@@ -831,8 +831,10 @@ hipError_t launch_split_waves(const SplitParams& sp, hipStream_t st)
 // means that a split is a single block; then only many rows on many blocks give
 // eight waves work (8 rows on 256 blocks: 19.6 us a call, with four waves 21.2;
 // otherwise four are 2 % faster), and of blocks of 32 or 64 keys one group is
-// enough for up to four rows (16 heads on 130 keys, block 32: 14.9 us with four
-// waves, 14.0 with one).
+// enough for a row per wave (8 heads on 1500 keys, block 32: 17.0 us a call with
+// four waves, 16.2 with one) or up to four rows on few blocks (16 heads on 130
+// keys, block 32: 14.9 and 14.0; on many the replay takes longer on one group:
+// 4 rows on 212 blocks of 64 21.1 and 21.6, of 32 21.2 and 24.6).
 template <int D, int BLK, int RT>
 hipError_t launch_split_rt(const SplitParams& sp, hipStream_t st)
 {
@@ -844,7 +846,9 @@ hipError_t launch_split_rt(const SplitParams& sp, hipStream_t st)
     const long long wgs = (flat + RT * kRows - 1) / (RT * kRows) * sp.nsplit * p.Hkv * p.B;
     if (wgs <= ncu && (RT == 2 || (flat > 4 && sp.nblk >= 128))) return launch_split_waves<D, BLK, RT, 8>(sp, st);
     if constexpr (RT == 1 && BLK < 128) {
-        if (sp.bps == 1 && flat <= 4) return launch_split_waves<D, BLK, RT, BLK / kSlotKeys>(sp, st);
+        constexpr int kFew = D == 64 && BLK == 64 ? 8 : 32;
+        if (sp.bps == 1 && (flat <= BLK / kSlotKeys || (flat <= 4 && sp.nblk <= kFew)))
+            return launch_split_waves<D, BLK, RT, BLK / kSlotKeys>(sp, st);
     }
     return launch_split_waves<D, BLK, RT, 4>(sp, st);
 }

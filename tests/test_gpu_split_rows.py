@@ -30,6 +30,9 @@ SHAPES = [
     ((1, 6, 2, 1, 650, 128, False, 64), (1, 2)),       # three rows
     ((1, 8, 1, 1, 5000, 64, True, 32), (1, 8)),        # eight rows, one block per split, 157 blocks to replay
     ((1, 16, 16, 1, 600, 64, True, 128), (1, 4)),      # one block per split, whose group has four waves
+    ((1, 8, 2, 1, 1050, 64, True, 32), (1, 4)),        # four rows on 33 blocks: past what one wave replays well
+    ((1, 4, 4, 1, 3000, 128, True, 32), (1, 1)),       # one row on 94 blocks: one wave again
+    ((1, 4, 1, 1, 520, 64, True, 64), (1, 4)),         # four rows on 9 blocks of 64 at D = 64
 ]
 IDS = ["x".join(map(str, s)) for s, _ in SHAPES]
 
